@@ -2,10 +2,12 @@
 // gradient) with the input tile staged once in LDS.
 //
 // The implicit GEMM gathers every input pixel nine times (once per filter
-// tap) from the caches.  Here a workgroup computes TH full output rows of one
-// image for BN output channels: it stages CC input channels of the TH+2
-// rows (with a zero border) in LDS, then every filter tap is an LDS read at a
-// constant offset from the lane's pixel.  The contraction runs on
+// tap) from the caches.  Here a workgroup computes a tile of output pixels --
+// TH full rows of one image (conv3x3_k), or BM consecutive pixels of a
+// replica (conv3x3_flat_k) -- for BN output channels: it stages 16 or 32
+// input channels of the pixels the tile touches (with a zero border) in LDS,
+// then every filter tap is an LDS read at a constant offset from the lane's
+// pixel.  The contraction runs on
 // v_mfma_f32_16x16x4f32: per MFMA the four lane groups (lane / 16) take four
 // consecutive input channels of the same tap; 16 consecutive output pixels
 // are the rows of the 16x16 block and 16 output channels its columns.
@@ -15,7 +17,7 @@
 // rotated by 180 degrees, which the weight loader applies (FLIP).
 //
 // Grid: as many workgroups as fit on the chip at once; each takes every G-th
-// tile (replica, output-channel tile, TH rows of one image) and prefetches
+// tile (replica, output-channel tile, pixels) and prefetches
 // the next tile's inputs while it computes.  Epilogues match the implicit
 // GEMM's: bias, ReLU and the batch-norm partial sums of the forward;
 // accumulate, residual add, ReLU mask and the batch-norm backward partial
@@ -30,6 +32,11 @@ namespace cbk {
 namespace {
 
 typedef float v4f __attribute__((ext_vector_type(4)));
+// Four floats in memory at any float's alignment, which a 16-byte load or
+// store of global memory allows: the stride-1 kernels' tensors need no more.
+typedef v4f v4a4 __attribute__((aligned(4)));
+
+inline unsigned cdiv(int64_t a, int64_t b) { return (unsigned)((a + b - 1) / b); }
 
 __device__ __forceinline__ v4f mfma4(float a, float b, v4f c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
@@ -244,10 +251,10 @@ __global__ __launch_bounds__(256) void conv3x3_k(DirectArgs a) {
 #pragma unroll
       for (int u = 0; u < TN; ++u) {
         const int64_t g = gofs(d, t, u);
-        if (a.mask) m[t][u] = *reinterpret_cast<const v4f*>(a.mask + g);
+        if (a.mask) m[t][u] = *reinterpret_cast<const v4a4*>(a.mask + g);
         if (a.bn_part) {
-          x[t][u] = *reinterpret_cast<const v4f*>(a.bn_x + g);
-          if (!RC && a.bn_y) y[t][u] = *reinterpret_cast<const v4f*>(a.bn_y + g);
+          x[t][u] = *reinterpret_cast<const v4a4*>(a.bn_x + g);
+          if (!RC && a.bn_y) y[t][u] = *reinterpret_cast<const v4a4*>(a.bn_y + g);
         }
       }
   };
@@ -286,11 +293,11 @@ __global__ __launch_bounds__(256) void conv3x3_k(DirectArgs a) {
             s1[u] += (double)e;
             s2[u] += (double)e * e;
           }
-          *reinterpret_cast<v4f*>(a.out + g) = v;
+          *reinterpret_cast<v4a4*>(a.out + g) = v;
         } else {
-          if (a.accumulate) v += *reinterpret_cast<const v4f*>(a.out + g);
+          if (a.accumulate) v += *reinterpret_cast<const v4a4*>(a.out + g);
           if (a.add_mode == ADD_SAME) {
-            v += *reinterpret_cast<const v4f*>(a.add + g);
+            v += *reinterpret_cast<const v4a4*>(a.add + g);
           } else if (a.add_mode == ADD_SUBSAMPLE) {
             const int st = a.add_st;
             const int p0 = d.oh0 * WW + (wave * TM + t) * 16 + 4 * kq;
@@ -315,7 +322,7 @@ __global__ __launch_bounds__(256) void conv3x3_k(DirectArgs a) {
             for (int i = 0; i < 4; ++i)
               if (!(e_mask[t][u][i] > 0.f)) v[i] = 0.f;
           }
-          *reinterpret_cast<v4f*>(a.out + g) = v;
+          *reinterpret_cast<v4a4*>(a.out + g) = v;
           if (a.bn_part) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
@@ -409,6 +416,355 @@ __global__ __launch_bounds__(256) void conv3x3_k(DirectArgs a) {
     if (!more) break;
     t += G;
     d = dn;
+  }
+}
+
+// The same convolutions at stride 1 with tiles of BM consecutive output
+// pixels of a replica (of one or more images) by BN channels, on four waves
+// of TM x TN fragments that split the pixels: for the widths whose rows do
+// not make whole 16-pixel fragments (7, 14, 28, 56), and for widths 8 and 16
+// where the tile can then be larger.  The input lies in LDS in a padded order
+// in which a tap is a constant step: image after image, each with one zero
+// row before it, rows with one zero pixel before each, so that the pixel
+// after a row's last and the row after an image's last are zeros too.
+template <int WW, int BM>
+struct DirectShape {
+  static constexpr int HW = WW * WW;
+  static constexpr int PW = WW + 1;                    // padded row
+  static constexpr int IMGS = (BM + HW - 2) / HW + 1;  // images a tile can touch
+  // A tile of whole rows of one image, or the most that BM pixels can span:
+  // a new row every WW, a zero row at every further image.
+  static constexpr bool ROWS = BM % WW == 0 && HW % BM == 0;
+  static constexpr int SPAN =
+      ROWS ? (BM / WW - 1) * PW + WW - 1 : ((BM - 1 + WW - 1) / WW + IMGS - 1) * PW + WW - 1;
+  static constexpr int NPIX = SPAN + 2 * PW + 3;
+  static constexpr int NPIXP = (NPIX + 15) / 16 * 16;
+  // padded position of the window corner of output pixel p of image img
+  __device__ static int corner(int img, int p) {
+    const int oh = p / WW, ow = p - oh * WW;
+    return (img * (WW + 1) + oh) * PW + ow;
+  }
+};
+
+template <int WW, int BM, int BN, bool FLIP, bool RC>
+__global__ __launch_bounds__(256, 2) void conv3x3_flat_k(DirectArgs a) {
+  static_assert(FLIP || !RC, "the mask recompute belongs to the data gradient");
+  using S = DirectShape<WW, BM>;
+  constexpr int HW = S::HW, PW = S::PW, NPIXP = S::NPIXP;
+  constexpr int TM = BM / 64, TN = BN / 16;  // the four waves split the pixels
+  static_assert(TM >= 1 && BM % 64 == 0 && BN % 16 == 0, "whole fragments");
+  constexpr int CC = 16, C4 = CC / 4;     // channels and channel quads per chunk
+  constexpr int NX = C4 * NPIXP, NXT = (NX + 255) / 256;  // input quads per chunk
+  constexpr int NW = BN * 9 * C4, NWT = (NW + 255) / 256; // filter quads per chunk
+  constexpr bool VEC = HW % 4 == 0;       // a lane's four pixels lie in one plane
+  // LDS holds four consecutive channels of a pixel (or of a filter row and
+  // tap) as one 16-byte quad, so that one ds_read_b128 gives a lane the
+  // operands of four MFMAs: within an MFMA group of 16 channels lane group kq
+  // takes channel 4 kq + q for MFMA q.  [channel quad][padded pixel] and
+  // [tap and channel quad][filter row]: the 16 lanes a read serves together
+  // (two quads' worth of rows) fall on distinct banks.  Filter rows are xored
+  // with the tap, so that the taps of one row, which neighbouring lanes
+  // store, do too.
+  // One copy: the next chunk waits in registers until every wave is done
+  // with this one.
+  __shared__ __attribute__((aligned(16))) v4f xs[C4 * NPIXP];
+  __shared__ __attribute__((aligned(16))) v4f ws[9 * C4 * BN];
+  __shared__ double red[4][BN][2];
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, kq = lane >> 4, l16 = lane & 15;
+  const int M = a.b * HW;                           // output pixels of a replica
+  const int rows_rep = (M + BM - 1) / BM;           // pixel tiles of one replica
+  const int per_rep = rows_rep * (a.Cout / BN);
+  const int T = a.k * per_rep;
+  const int nchunk = a.Cin / CC;
+
+  // Tile t: replica, pixel tile, then output-channel tile, so that the tiles
+  // reading one input tile are numbered together and, with the XCD-major
+  // numbering below, fetch it into one XCD's L2.
+  struct Tile {
+    int j, co0, rt, m0;
+  };
+  auto decode = [&](int t) {
+    Tile d;
+    d.j = t / per_rep;
+    const int r = t - d.j * per_rep;
+    d.rt = r / (a.Cout / BN);
+    d.co0 = (r - d.rt * (a.Cout / BN)) * BN;
+    d.m0 = d.rt * BM;
+    return d;
+  };
+
+  // Byte offsets of this thread's quads for a tile's first chunk: input quads
+  // (their first channel; from the tile's first image), filter quads.
+  uint32_t xo[NXT], wo[NWT];
+  auto offsets = [&](const Tile& d) {
+    const int img0 = d.m0 / HW, v0 = S::corner(0, d.m0 - img0 * HW);
+#pragma unroll
+    for (int u = 0; u < NXT; ++u) {
+      const int e = tid + u * 256, c4 = e / NPIXP, v = v0 + e - c4 * NPIXP;
+      const int row = v / PW, iw = v - row * PW - 1, im = row / (WW + 1), ih = row - im * (WW + 1) - 1;
+      const bool ok = (NX % 256 == 0 || e < NX) && ih >= 0 && iw >= 0 && img0 + im < a.b && im < S::IMGS;
+      xo[u] = ok ? (uint32_t)((im * a.Cin + c4 * 4) * HW + ih * WW + iw) * 4u : OUTSIDE;
+    }
+#pragma unroll
+    for (int u = 0; u < NWT; ++u) {
+      // forward: filter [co0 + row][4 c4 ..][tap]; flipped: filter
+      // [4 c4 ..][co0 + row][tap]; both enumerated along memory
+      const int e = tid + u * 256, tap = e % 9, q = e / 9;
+      const int row = FLIP ? q % BN : q / C4, c4 = FLIP ? q / BN : q % C4;
+      const int el = FLIP ? (4 * c4 * a.Cout + d.co0 + row) * 9 + tap
+                          : ((d.co0 + row) * a.Cin + 4 * c4) * 9 + tap;
+      wo[u] = (NW % 256 == 0 || e < NW) ? (uint32_t)el * 4u : OUTSIDE;
+    }
+  };
+  v4f rx[NXT], rw[NWT];
+  auto load = [&](const Tile& d, int c0) {
+    const int img0 = d.m0 / HW;
+    const auto src = buf_rsrc_u(a.in + ((int64_t)(d.j * a.b + img0) * a.Cin) * HW,
+                                (uint32_t)(min(a.b - img0, S::IMGS) * a.Cin * HW) * 4u);
+    const auto wsrc = buf_rsrc_u(a.w + (int64_t)d.j * a.pstride, (uint32_t)(a.Cin * a.Cout) * 36u);
+#pragma unroll
+    for (int u = 0; u < NXT; ++u)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) rx[u][i] = buf_ld_s(src, xo[u], (uint32_t)((c0 + i) * HW) * 4u);
+    const uint32_t step = FLIP ? (uint32_t)a.Cout * 36u : 36u;
+#pragma unroll
+    for (int u = 0; u < NWT; ++u)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) rw[u][i] = buf_ld_s(wsrc, wo[u], (uint32_t)(c0 + i) * step);
+  };
+  auto store = [&]() {
+#pragma unroll
+    for (int u = 0; u < NXT; ++u) {
+      const int e = tid + u * 256;
+      if (NX % 256 == 0 || e < NX) xs[e] = rx[u];
+    }
+#pragma unroll
+    for (int u = 0; u < NWT; ++u) {
+      const int e = tid + u * 256, tap = e % 9, q = e / 9;
+      const int row = FLIP ? q % BN : q / C4, c4 = FLIP ? q / BN : q % C4;
+      const int tp = FLIP ? 8 - tap : tap;
+      if (NW % 256 == 0 || e < NW) ws[(tp * C4 + c4) * BN + (row ^ tp)] = rw[u];
+    }
+  };
+
+  int xb[TM];
+  const v4f* wb = ws + kq * BN;
+  auto bases = [&](const Tile& d) {
+    const int img0 = d.m0 / HW, v0 = S::corner(0, d.m0 - img0 * HW);
+#pragma unroll
+    for (int x = 0; x < TM; ++x) {
+      const int m = min(d.m0 + (wave * TM + x) * 16 + l16, M - 1), img = m / HW;
+      xb[x] = kq * NPIXP + S::corner(img - img0, m - img * HW) - v0;
+    }
+  };
+
+  // The contraction runs over (chunk, tap, q), the order of the implicit
+  // GEMM's tap-major loaders with 16-step stages.
+  v4f acc[TN][TM];
+  auto multiply = [&]() {
+#pragma unroll
+    for (int tap = 0; tap < 9; ++tap) {
+      v4f av[TM], bv[TN];
+#pragma unroll
+      for (int x = 0; x < TM; ++x) av[x] = xs[xb[x] + (tap / 3) * PW + tap % 3];
+#pragma unroll
+      for (int y = 0; y < TN; ++y) bv[y] = wb[(l16 ^ tap) + tap * C4 * BN + y * 16];
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int y = 0; y < TN; ++y)
+#pragma unroll
+          for (int x = 0; x < TM; ++x) acc[y][x] = mfma4(av[x][q], bv[y][q], acc[y][x]);
+    }
+  };
+
+  // The lane's four consecutive pixels of block (x, y): element offset of the
+  // first, and whether it exists.
+  auto gofs = [&](const Tile& d, int x, int y, bool& ok) {
+    const int m = d.m0 + (wave * TM + x) * 16 + 4 * kq;
+    const int co = d.co0 + y * 16 + l16;
+    ok = S::ROWS || m < M;
+    const int mm = ok ? m : 0, img = mm / HW;
+    return (int64_t)((d.j * a.b + img) * a.Cout + co) * HW + mm - img * HW;
+  };
+  auto ld4 = [&](const float* base, int64_t g) { return *reinterpret_cast<const v4a4*>(base + g); };
+
+  // Epilogue operands of the data gradient (the ReLU mask or the next batch
+  // norm's y, and its x), loaded before the tile's last chunk of MFMAs, so
+  // their latency overlaps that chunk (after it where the wave's tile fills
+  // the registers).
+  constexpr bool PRE = TM * TN <= 4;
+  v4f e_k[TN][TM], e_x[TN][TM];
+  const float* keep = RC ? nullptr : a.mask ? a.mask : a.bn_part ? a.bn_y : nullptr;
+  auto prefetch_epilogue = [&](const Tile& d) {
+    if (!FLIP || !VEC) return;
+#pragma unroll
+    for (int y = 0; y < TN; ++y)
+#pragma unroll
+      for (int x = 0; x < TM; ++x) {
+        bool ok;
+        const int64_t g = gofs(d, x, y, ok);
+        if (keep) e_k[y][x] = ld4(keep, g);
+        if (a.bn_part) e_x[y][x] = ld4(a.bn_x, g);
+      }
+  };
+
+  auto epilogue = [&](const Tile& d) {
+    // acc[y][x][i] is pixel (wave TM + x) 16 + 4 kq + i, channel
+    // co0 + 16 y + lane % 16 of the tile
+    double s1[TN], s2[TN];
+#pragma unroll
+    for (int y = 0; y < TN; ++y) {
+      s1[y] = s2[y] = 0.0;
+      const int co = d.co0 + y * 16 + l16;
+      float bv = 0.f, bm = 0.f, bi = 0.f, ga = 0.f, be = 0.f;
+      if (!FLIP && a.bias) bv = a.bias[(int64_t)d.j * a.pstride + co];
+      if (FLIP && a.bn_part) {
+        bm = a.bn_mean[d.j * a.Cout + co];
+        bi = a.bn_istd[d.j * a.Cout + co];
+      }
+      if (RC) {
+        ga = a.bn_gamma[(int64_t)d.j * a.pstride + co];
+        be = a.bn_gamma[(int64_t)d.j * a.pstride + a.Cout + co];
+      }
+      // One output element of the data gradient (dX index g, image pixel p)
+      // from its operands; returns what is stored.
+      auto element = [&](float v, int64_t g, int img, int p, float kv, float xv, float yv) {
+        if (a.add_mode == ADD_SUBSAMPLE) {
+          const int st = a.add_st, ih = p / WW, iw = p - ih * WW;
+          if (ih % st == 0 && iw % st == 0)
+            v += a.add[(((int64_t)(d.j * a.b + img) * a.add_C + co) * ((WW + st - 1) / st) + ih / st) *
+                           ((WW + st - 1) / st) + iw / st];
+        }
+        bool on = true;
+        if (RC) on = bn_affine(xv, bm, bi, ga, be) > 0.f;
+        if (RC ? (a.rc_mask && !on) : (a.mask && !(kv > 0.f))) v = 0.f;
+        if (a.bn_part) {
+          if (!RC) on = !a.bn_y || yv > 0.f;
+          const float dd = on ? v : 0.f, xh = (xv - bm) * bi;
+          s1[y] += (double)dd;
+          s2[y] += (double)dd * xh;
+        }
+        return v;
+      };
+#pragma unroll
+      for (int x = 0; x < TM; ++x) {
+        bool ok;
+        const int64_t g = gofs(d, x, y, ok);
+        v4f v = acc[y][x];
+        const int m = d.m0 + (wave * TM + x) * 16 + 4 * kq;
+        if (!ok) continue;
+        if (VEC) {
+          if (!FLIP) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              float e = v[i] + bv;
+              if (a.relu) e = e > 0.f ? e : 0.f;
+              v[i] = e;
+              s1[y] += (double)e;
+              s2[y] += (double)e * e;
+            }
+          } else {
+            if (a.accumulate) v += ld4(a.out, g);
+            if (a.add_mode == ADD_SAME) v += ld4(a.add, g);
+            // with both a mask and bn_y given, bn_y is read here
+            const v4f yv = !RC && a.bn_part && a.mask && a.bn_y ? ld4(a.bn_y, g) : e_k[y][x];
+            const int img = m / HW, p = m - img * HW;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] = element(v[i], g + i, img, p + i, e_k[y][x][i], e_x[y][x][i], yv[i]);
+          }
+          *reinterpret_cast<v4a4*>(a.out + g) = v;
+          continue;
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          if (m + i >= M) continue;
+          const int img = (m + i) / HW, p = m + i - img * HW;
+          const int64_t gi = (int64_t)((d.j * a.b + img) * a.Cout + co) * HW + p;
+          float e = v[i];
+          if (!FLIP) {
+            e += bv;
+            if (a.relu) e = e > 0.f ? e : 0.f;
+            s1[y] += (double)e;
+            s2[y] += (double)e * e;
+          } else {
+            if (a.accumulate) e += a.out[gi];
+            if (a.add_mode == ADD_SAME) e += a.add[gi];
+            e = element(e, gi, img, p, a.mask ? a.mask[gi] : 0.f, a.bn_part ? a.bn_x[gi] : 0.f,
+                        !RC && a.bn_part && a.bn_y ? a.bn_y[gi] : 0.f);
+          }
+          a.out[gi] = e;
+        }
+      }
+    }
+    double* part = FLIP ? a.bn_part : a.stats;
+    if (!part) return;
+    // per-channel partial sums of the tile: lanes of a column by xor
+    // butterfly, then the four waves in order.  (Every chunk ends
+    // with a barrier, so the previous tile's reads of red are done.)
+#pragma unroll
+    for (int y = 0; y < TN; ++y) {
+      double u = s1[y], v = s2[y];
+      u += shfl_xor_d(u, 16);
+      v += shfl_xor_d(v, 16);
+      u += shfl_xor_d(u, 32);
+      v += shfl_xor_d(v, 32);
+      if (lane < 16) {
+        red[wave][y * 16 + lane][0] = u;
+        red[wave][y * 16 + lane][1] = v;
+      }
+    }
+    __syncthreads();
+    if (tid < BN) {
+      double u = red[0][tid][0], v = red[0][tid][1];
+#pragma unroll
+      for (int w = 1; w < 4; ++w) {
+        u += red[w][tid][0];
+        v += red[w][tid][1];
+      }
+      double* o = part + (((int64_t)d.j * a.Cout + d.co0 + tid) * rows_rep + d.rt) * 2;
+      o[0] = u;
+      o[1] = v;
+    }
+  };
+
+  // Workgroup w takes tiles w, w + G, w + 2G, ...  Every (tile, chunk) item
+  // prefetches the next item's inputs into registers before its MFMAs.
+  const int G = gridDim.x;
+  int t = xcd_major(blockIdx.x, G);
+  Tile d = decode(t);
+  offsets(d);
+  bases(d);
+  load(d, 0);
+  store();
+  __syncthreads();
+  while (true) {
+#pragma unroll
+    for (int y = 0; y < TN; ++y)
+#pragma unroll
+      for (int x = 0; x < TM; ++x) acc[y][x] = v4f{0.f, 0.f, 0.f, 0.f};
+    const bool more = t + G < T;
+    const Tile dn = more ? decode(t + G) : d;
+    for (int c = 0; c < nchunk; ++c) {
+      const bool last = c + 1 == nchunk;
+      const bool has_next = !last || more;
+      if (last && more) offsets(dn);
+      if (has_next) load(last ? dn : d, last ? 0 : (c + 1) * CC);
+      if (last && PRE) prefetch_epilogue(d);
+      multiply();
+      if (has_next) {
+        __syncthreads();
+        store();
+      }
+      __syncthreads();
+    }
+    if (!PRE) prefetch_epilogue(d);
+    epilogue(d);
+    if (!more) break;
+    t += G;
+    d = dn;
+    bases(d);
   }
 }
 
@@ -901,6 +1257,31 @@ hipError_t launch(const DirectArgs& a, hipStream_t s, const char** name) {
   return hipGetLastError();
 }
 
+template <int WW, int BM, int BN, bool FLIP, bool RC>
+hipError_t launch_flat(const DirectArgs& a, hipStream_t s, const char** name) {
+  static int resident = 0;
+  if (!resident) {
+    int per_cu = 0, cus = 0, dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, conv3x3_flat_k<WW, BM, BN, FLIP, RC>,
+                                                     256, 0) != hipSuccess)
+      return hipErrorInvalidValue;
+    resident = std::max(1, per_cu) * std::max(1, cus);
+  }
+  const int64_t T = (int64_t)a.k * cdiv((int64_t)a.b * WW * WW, BM) * (a.Cout / BN);
+  const int64_t per = (T + resident - 1) / resident;
+  const int64_t G = (T + per - 1) / per;
+  klaunch(conv3x3_flat_k<WW, BM, BN, FLIP, RC>, dim3((unsigned)G), dim3(256), 0, s, a);
+  if (name) {
+    static const std::string n = std::string("conv3x3_flat_k<") + std::to_string(WW) + ", " +
+                                 std::to_string(BM) + ", " + std::to_string(BN) + ", " +
+                                 (FLIP ? "true" : "false") + ", " + (RC ? "true" : "false") + ">";
+    *name = n.c_str();
+  }
+  return hipGetLastError();
+}
+
 // Built for square images of width 8, 16 or 32 and channel counts that
 // are multiples of 16.  Tile choice: 16 output channels and TH output rows
 // (a multiple of 64 pixels), the taller TH if it still gives every CU two
@@ -913,10 +1294,78 @@ struct DirectTile {
 
 constexpr int64_t DIRECT_MIN_WGS = 512;
 
-bool direct_ok(int H, int W, int Cin, int Cout, int R, int st, int pad) {
-  if (R != 3 || st != 1 || pad != 1 || H != W) return false;
-  if (W != 8 && W != 16 && W != 32) return false;
-  return Cin % 16 == 0 && Cout % 16 == 0;
+bool direct_small(int W) { return W == 8 || W == 16 || W == 32; }
+
+// Widths 7, 14, 28 and 56 (flat tiles only) take over from the implicit GEMM
+// where that would use its 128 x 64 tiles (more than 32 output channels and
+// 128 such tiles); its smaller tiles stay ahead on smaller layers.  56 only
+// forward: the data gradient took 182 us against the GEMM's 177.
+bool direct_large(int k, int b, int W, int Cout, bool flip) {
+  if (W != 7 && W != 14 && W != 28 && (W != 56 || flip)) return false;
+  return Cout % 32 == 0 && Cout > 32 &&
+         (int64_t)k * cdiv((int64_t)b * W * W, 128) * cdiv(Cout, 64) >= DIRECT_MIN_WGS / 4;
+}
+
+bool direct_ok(const ConvGeom& g, bool flip) {
+  if (g.R != 3 || g.S != 3 || g.st != 1 || g.pad != 1 || g.H != g.W) return false;
+  const int Cin = flip ? g.Co : g.Ci, Cout = flip ? g.Ci : g.Co;
+  if (Cin % 16 || Cout % 16) return false;
+  // the buffers of one tile (the filter, the up to four images a flat tile
+  // touches) have 32-bit offsets below OUTSIDE
+  if ((int64_t)Cin * Cout * 36 >= OUTSIDE || (int64_t)Cin * g.H * g.W * 16 >= OUTSIDE) return false;
+  return direct_small(g.W) || direct_large(g.k, g.b, g.W, Cout, flip);
+}
+
+struct FlatTile {
+  int bm, bn;
+};
+
+// Flat tile of a stride-1 layer (output pixels by output channels), or {0, 0}
+// for the row tiles below.  A larger tile stages fewer operand values per
+// MFMA, so it is taken as long as it still gives every CU two workgroups
+// (DIRECT_MIN_WGS) over all replicas.  Per launch, forward / data gradient
+// with a batch norm's sums, us, the kernel it replaces in brackets:
+//   ResNet-32's 8x8, 64 channels: 64x16 at k=1 b=16 8.6 / 9.0 (8.9 / 9.6) and at
+//     k=4 b=32 11.0 / 10.9 (11.3 / 11.9), 128x16 at k=32 b=16 28.1 / 30.2 (33.6 /
+//     33.8)
+//   its 16x16, 32 channels: at k=32 b=16 256x32 forward 28.2 (30.9), 128x32 data
+//     gradient 33 (34); with fewer images the row tiles are ahead (k=4 b=32
+//     10.2 / 11.2 against 128x16's 10.4 / 11.6), and so they are at 32x32
+//   ResNet-50, k=2 b=32: 56 128x32 168 (185), 28 256x32 162 / 164 (188 / 179),
+//     14 256x32 159 / 159 (198 / 209), 7 128x16 165 / 168 (286 / 285)
+FlatTile flat_tile(int k, int b, int W, int Cout, bool flip) {
+  auto enough = [&](int bm, int bn) {
+    return (int64_t)k * cdiv((int64_t)b * W * W, bm) * (Cout / bn) >= DIRECT_MIN_WGS;
+  };
+  switch (W) {
+    case 7: return {128, 16};
+    case 8: return {enough(128, 16) ? 128 : 64, 16};
+    case 14:
+    case 28: return {256, 32};
+    case 56: return {128, 32};
+    case 16: {
+      const int bm = flip ? 128 : 256;
+      if (Cout % 32 == 0 && enough(bm, 32)) return {bm, 32};
+      return {0, 0};
+    }
+    default: return {0, 0};
+  }
+}
+
+template <bool FLIP, bool RC>
+hipError_t dispatch_flat(const DirectArgs& a, int W, FlatTile t, hipStream_t s, const char** name) {
+  switch (W) {
+    case 7: return launch_flat<7, 128, 16, FLIP, RC>(a, s, name);
+    case 8:
+      if (t.bm == 128) return launch_flat<8, 128, 16, FLIP, RC>(a, s, name);
+      return launch_flat<8, 64, 16, FLIP, RC>(a, s, name);
+    case 14: return launch_flat<14, 256, 32, FLIP, RC>(a, s, name);
+    case 16: return launch_flat<16, FLIP ? 128 : 256, 32, FLIP, RC>(a, s, name);
+    case 28: return launch_flat<28, 256, 32, FLIP, RC>(a, s, name);
+    default: break;
+  }
+  if constexpr (!FLIP) return launch_flat<56, 128, 32, FLIP, RC>(a, s, name);
+  return hipErrorInvalidValue;
 }
 
 // The forward at width 32 takes 8 rows (4 if that leaves too few
@@ -943,11 +1392,16 @@ hipError_t dispatch_w(const DirectArgs& a, DirectTile t, hipStream_t s, const ch
 // W: the output width
 template <bool FLIP, bool RC, int ST = 1>
 hipError_t dispatch(const DirectArgs& a, int W, hipStream_t s, const char** name) {
+  if constexpr (ST == 1) {
+    const FlatTile f = flat_tile(a.k, a.b, W, a.Cout, FLIP);
+    if (f.bm) return dispatch_flat<FLIP, RC>(a, W, f, s, name);
+  }
   const DirectTile t = direct_pick(a.k, a.b, W, a.Cout, FLIP);
   if constexpr (ST == 1)
     if (W == 32) return dispatch_w<FLIP, RC, ST, 32>(a, t, s, name);
   if (W == 16) return dispatch_w<FLIP, RC, ST, 16>(a, t, s, name);
-  return dispatch_w<FLIP, RC, ST, 8>(a, t, s, name);
+  if constexpr (ST == 2) return dispatch_w<FLIP, RC, ST, 8>(a, t, s, name);
+  return hipErrorInvalidValue;
 }
 
 // Weight gradient: units of 4 or 8 rows (below), so that a workgroup
@@ -1014,7 +1468,7 @@ bool direct_s2_ok(const ConvGeom& g) {
 }
 
 bool conv_direct_wgrad_ok(const ConvGeom& g) {
-  return direct_ok(g.H, g.W, g.Ci, g.Co, g.R, g.st, g.pad) || direct_s2_ok(g);
+  return (direct_small(g.W) && direct_ok(g, false)) || direct_s2_ok(g);
 }
 
 int conv_direct_wgrad_splits(const ConvGeom& g) {
@@ -1041,18 +1495,23 @@ hipError_t conv_direct_wgrad(const ConvBwdWeightArgs& w, hipStream_t s, const ch
 
 
 bool conv_direct_fwd_ok(const ConvGeom& g) {
-  return direct_ok(g.H, g.W, g.Ci, g.Co, g.R, g.st, g.pad) || direct_s2_ok(g);
+  return direct_ok(g, false) || direct_s2_ok(g);
 }
 
 bool conv_direct_bwd_data_ok(const ConvGeom& g) {
-  return direct_ok(g.H, g.W, g.Co, g.Ci, g.R, g.st, g.pad);
+  return direct_ok(g, true);
 }
 
 int conv_direct_fwd_tiles(const ConvGeom& g) {
+  if (g.st == 1)
+    if (const int bm = flat_tile(g.k, g.b, g.Wo, g.Co, false).bm)
+      return (int)cdiv((int64_t)g.b * g.Ho * g.Wo, bm);
   return g.b * (g.Ho / direct_pick(g.k, g.b, g.Wo, g.Co, false).th);
 }
 
 int conv_direct_bwd_data_tiles(const ConvGeom& g) {
+  if (const int bm = flat_tile(g.k, g.b, g.W, g.Ci, true).bm)
+    return (int)cdiv((int64_t)g.b * g.H * g.W, bm);
   return g.b * (g.H / direct_pick(g.k, g.b, g.W, g.Ci, true).th);
 }
 

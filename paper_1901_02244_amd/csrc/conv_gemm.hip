@@ -1314,9 +1314,7 @@ hipError_t conv_fwd(const ConvFwdArgs& a, hipStream_t s, const char** name) {
       klaunch(fc_fwd_mfma_k<4>, grid, block, 0, s, a.x, a.w, a.bias, a.pstride, a.g.b, a.g.Ci, a.g.Co, a.relu, a.y);
     return hipGetLastError();
   }
-  // the direct kernel moves its outputs in 16-byte pieces (workspace
-  // tensors are 256-byte aligned, so layers of a plan always qualify)
-  if (conv_direct_fwd_ok(a.g) && al16(a.y)) return conv_direct_fwd(a, s, name);
+  if (conv_direct_fwd_ok(a.g)) return conv_direct_fwd(a, s, name);
   switch (a.g.R) {
     case 1: return fwd_r<1>(a, s, name);
     case 3: return fwd_r<3>(a, s, name);
@@ -1346,8 +1344,8 @@ hipError_t conv_bwd_data(const ConvBwdDataArgs& a, hipStream_t s, const char** n
       klaunch(fc_dgrad_mfma_k<4>, grid, block, 0, s, a.dy, a.w, a.pstride, a.g.b, a.g.Ci, a.g.Co, a.accumulate, a.mask, a.dx);
     return hipGetLastError();
   }
+  if (conv_direct_bwd_data_ok(a.g)) return conv_direct_bwd_data(a, s, name);
   const bool vec_ok = al16(a.dx) && al16(a.mask) && al16(a.bn_x) && al16(a.bn_y) && al16(a.add);
-  if (conv_direct_bwd_data_ok(a.g) && vec_ok) return conv_direct_bwd_data(a, s, name);
   if (conv_s2_dgrad_ok(a.g) && vec_ok && (a.add_mode != ADD_SUBSAMPLE || a.add_st == 2))
     return conv_s2_dgrad(a, s, name);
   const int key = a.g.R * 10 + a.g.st;

@@ -60,6 +60,12 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buf_rsrc_u(const float* base, 
 __device__ __forceinline__ float buf_ld(__amdgpu_buffer_rsrc_t r, uint32_t off_bytes) {
   return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, off_bytes, 0, 0));
 }
+// The same with a wave-uniform byte offset that every lane adds.
+__device__ __forceinline__ float buf_ld_s(__amdgpu_buffer_rsrc_t r, uint32_t off_bytes,
+                                          uint32_t uniform_bytes) {
+  return __builtin_bit_cast(float,
+                            __builtin_amdgcn_raw_buffer_load_b32(r, off_bytes, uniform_bytes, 0));
+}
 typedef float buf_v4f __attribute__((ext_vector_type(4)));
 // four consecutive floats; the whole quad reads 0 when it starts at or past `bytes`
 __device__ __forceinline__ buf_v4f buf_ld4(__amdgpu_buffer_rsrc_t r, uint32_t off_bytes) {
@@ -172,10 +178,11 @@ hipError_t conv_bwd_data(const ConvBwdDataArgs& a, hipStream_t s, const char** n
 hipError_t conv_bwd_weight(const ConvBwdWeightArgs& a, hipStream_t s,
                            const char** name = nullptr);
 // 3x3 stride-1 pad-1 convolutions on 8/16/32-wide square images with
-// channel counts that are multiples of 16 run on a direct kernel (input
-// tile staged once in LDS); conv_fwd / conv_bwd_data route there
-// themselves.  *_tiles give its number of row tiles per replica (the count
-// of batch-norm partial sums its epilogue writes).
+// channel counts that are multiples of 16, and the larger ones on
+// 7/14/28/56-wide images (conv_direct.hip's direct_large), run on a direct
+// kernel (input tile staged once in LDS); conv_fwd / conv_bwd_data route
+// there themselves.  *_tiles give its number of pixel tiles per replica (the
+// count of batch-norm partial sums its epilogue writes).
 bool conv_direct_fwd_ok(const ConvGeom& g);
 bool conv_direct_bwd_data_ok(const ConvGeom& g);
 int conv_direct_fwd_tiles(const ConvGeom& g);

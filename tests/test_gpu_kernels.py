@@ -575,3 +575,70 @@ def test_conv_data_gradient_epilogue(case):
             s2 = (dd * xh).sum(axis=(0, 2, 3))
             assert max_rel(sums[j, :, 0], s1) <= TOL_STEP1, (name, j, "sum d")
             assert max_rel(sums[j, :, 1], s2) <= TOL_STEP1, (name, j, "sum d*xh")
+
+
+# 3x3 stride-1 layers on the direct kernel's flat pixel tiles: per width the
+# fewest channels at these batches that reach each tile (one case below the
+# 14-wide rule stays on the GEMM), with last tiles that are partial and tiles
+# that span two or more images
+FLAT = [
+    ("flat.w7", 3, 9, 16, 7, 704, 3, 1, 1, 1, 1, 1),
+    ("flat.w8.bm128", 2, 31, 16, 8, 256, 3, 1, 1, 0, 1, 1),
+    ("flat.w14", 2, 5, 32, 14, 512, 3, 1, 1, 0, 0, 1),
+    ("flat.w14.below", 2, 5, 32, 14, 448, 3, 1, 1, 0, 0, 1),
+    ("flat.w16", 2, 16, 16, 16, 512, 3, 1, 1, 1, 0, 1),
+    ("flat.w28", 1, 3, 16, 28, 448, 3, 1, 1, 1, 1, 1),
+    ("flat.w56", 1, 1, 48, 56, 352, 3, 1, 1, 0, 1, 1),
+]
+
+# columns as in DGRAD_EPILOGUE
+FLAT_DGRAD = [
+    ("flat.w7.acc.mask.same.bn", 3, 9, 704, 7, 16, 3, 1, 1, 1, 1, 1, 704, 1, 1),
+    ("flat.w7.sub.bn.rc", 3, 9, 704, 7, 16, 3, 1, 1, 0, 1, 2, 704, 1, 3),
+    ("flat.w8.bm128.same.bn", 2, 31, 256, 8, 16, 3, 1, 1, 0, 0, 1, 256, 1, 1),
+    ("flat.w14.mask.bn", 2, 5, 512, 14, 32, 3, 1, 1, 0, 1, 0, 0, 1, 0),
+    ("flat.w14.acc.sub.bn.relux", 2, 5, 512, 14, 16, 3, 1, 1, 1, 0, 2, 512, 1, 2),
+    ("flat.w16.mask.bn.rc", 2, 8, 512, 16, 16, 3, 1, 1, 0, 1, 0, 0, 1, 3),
+    ("flat.w28.same", 1, 3, 448, 28, 16, 3, 1, 1, 0, 1, 1, 448, 0, 0),
+]
+
+
+@pytest.mark.parametrize("case", FLAT + FLAT_DGRAD, ids=[c[0] for c in FLAT + FLAT_DGRAD])
+def test_conv_flat_tiles(case):
+    (test_conv_kernels if len(case) == 12 else test_conv_data_gradient_epilogue)(case)
+
+
+@pytest.mark.parametrize("W,C", [(14, 512), (16, 32), (32, 16)])
+def test_direct_conv_at_any_float_alignment(W, C):
+    """The stride-1 direct kernels move four floats at a time at any float's
+    alignment: tensors one float past a 16-byte boundary give the same bytes
+    (forward with statistics, data gradient with batch-norm sums)."""
+    L, k, b, s = cb.lib(), 2, 5, torch.cuda.current_stream().cuda_stream
+    n, nw = k * b * C * W * W, C * C * 9
+    parts = L.cb_test_conv_fwd_parts(k, b, C, W, W, C, 3, 1, 1)
+    dparts = L.cb_test_conv_dgrad_parts(k, b, C, W, W, C, 3, 1, 1)
+    g = torch.Generator(device="cuda").manual_seed(W)
+    src = torch.randn(5, n, device="cuda", generator=g)
+    w = torch.randn(k * nw, device="cuda", generator=g)
+    m = torch.rand(2, k * C, device="cuda", generator=g) + 0.5
+    scratch_n = L.cb_test_conv_scratch_bytes(k, b, C, W, W, C, 3, 1, 1)
+    scratch = torch.empty(scratch_n, dtype=torch.uint8, device="cuda")
+    gw = torch.empty_like(w)
+    outs = []
+    for off in (0, 1):
+        x, dy, mask, add, bnx = (torch.empty(n + 4, device="cuda")[off:off + n].copy_(t) for t in src)
+        y, dx = (torch.full((n + 4,), float("nan"), device="cuda")[off:off + n] for _ in range(2))
+        st = torch.full((k * C * parts * 2,), float("nan"), dtype=torch.float64, device="cuda")
+        pt = torch.full((k * C * dparts * 2,), float("nan"), dtype=torch.float64, device="cuda")
+        # the weight gradient needs an aligned dY on the 16- and 32-wide layers
+        assert L.cb_test_conv(k, b, C, W, W, C, 3, 1, 1, 0, 0, x.data_ptr(), w.data_ptr(), nw,
+                              y.data_ptr(), st.data_ptr(), src[1].data_ptr(), None, gw.data_ptr(),
+                              scratch.data_ptr(), scratch_n, s) == 0
+        assert L.cb_test_conv_dgrad(k, b, C, W, W, C, 3, 1, 1, dy.data_ptr(), w.data_ptr(), nw,
+                                    dx.data_ptr(), 0, mask.data_ptr(), add.data_ptr(), 1, C,
+                                    bnx.data_ptr(), None, m[0].data_ptr(), m[1].data_ptr(), None,
+                                    pt.data_ptr(), s) == 0
+        torch.cuda.synchronize()
+        outs.append([t.cpu().numpy() for t in (y, st, dx, pt)])
+    for a, c in zip(*outs):
+        assert np.isfinite(a).all() and np.array_equal(a, c)
