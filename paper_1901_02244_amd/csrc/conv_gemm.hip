@@ -12,7 +12,7 @@
 // learner's batch is small (Sec. 3.1: learners train independently).
 //
 // Tiling: 256 threads (4 wave64s), LDS stages of BK contraction steps
-// stored with k contiguous, so each 16x16x4 MFMA operand group is one
+// stored as quads of four steps, so each 16x16x4 MFMA operand group is one
 // ds_read_b128; within a group of 16 steps the contraction index seen by
 // lane l at sub-step kk is 4*(l/16) + kk for both operands.  Global loads
 // for the next stage are in flight while the current stage is multiplied
@@ -54,21 +54,31 @@ __device__ __forceinline__ GemmTile gemm_tile() {
   return r;
 }
 
-// One LDS stage: As[rows][BK+4], Bs[cols][BK+4], both k-contiguous.
-template <int TM, int TN, int BK>
-__device__ __forceinline__ void mma_stage(const float* As, const float* Bs, int wm0, int wn0,
+// LDS layout of an operand stage of ROWS rows (a multiple of 16): quad of four
+// contraction steps by row, 16 bytes each, the row xored with a swizzle of
+// the quad.  The 16 lanes that a 16-byte read serves together take lanes 0-3
+// and 12-15 of one quad's 16 rows and 4-11 of the next one's, and those of a
+// write that stores four quads per row four rows of each: both fall on
+// distinct banks.  (Rows padded to BK + 4 floats had 0.5 to 0.65 conflict
+// cycles per useful one, and a fifth more LDS.)
+template <int ROWS>
+__device__ __forceinline__ int quad_at(int row, int quad) {
+  return quad * ROWS + (row ^ (0x84c0 >> (4 * (quad & 3)) & 12));
+}
+
+// One LDS stage: the products of A rows wm0 + 16 i and B rows wn0 + 16 i.
+template <int BM, int BN, int TM, int TN, int BK>
+__device__ __forceinline__ void mma_stage(const v4f* As, const v4f* Bs, int wm0, int wn0,
                                           int lane, v4f (&acc)[TM][TN]) {
-  constexpr int LDK = BK + 4;
-  const int r = lane & 15, q = (lane >> 4) * 4;
+  const v4f* Ar = As + quad_at<BM>(wm0 + (lane & 15), lane >> 4);
+  const v4f* Br = Bs + quad_at<BN>(wn0 + (lane & 15), lane >> 4);
 #pragma unroll
   for (int g = 0; g < BK; g += 16) {
     v4f av[TM], bv[TN];
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
-      av[i] = *reinterpret_cast<const v4f*>(As + (wm0 + i * 16 + r) * LDK + g + q);
+    for (int i = 0; i < TM; ++i) av[i] = Ar[g / 4 * BM + i * 16];
 #pragma unroll
-    for (int i = 0; i < TN; ++i)
-      bv[i] = *reinterpret_cast<const v4f*>(Bs + (wn0 + i * 16 + r) * LDK + g + q);
+    for (int i = 0; i < TN; ++i) bv[i] = Br[g / 4 * BN + i * 16];
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk)
 #pragma unroll
@@ -77,6 +87,20 @@ __device__ __forceinline__ void mma_stage(const float* As, const float* Bs, int 
         for (int b = 0; b < TN; ++b) acc[a][b] = mfma4(av[a][kk], bv[b][kk], acc[a][b]);
   }
 }
+
+// The lane's blocks of four consecutive rows m of a tile, 16 apart, as
+// (image, pixel) of planes of HW pixels: one division, then steps.
+struct RowIter {
+  int img, p;
+  __device__ __forceinline__ RowIter(int m, int HW) : img(m / HW), p(m - m / HW * HW) {}
+  __device__ __forceinline__ void step16(int HW) {
+    p += 16;
+    while (p >= HW) {
+      p -= HW;
+      ++img;
+    }
+  }
+};
 
 __device__ __forceinline__ float relu0(float v) { return v > 0.f ? v : 0.f; }
 
@@ -93,15 +117,14 @@ __device__ __forceinline__ double shfl_xor_d(double v, int o) { return __shfl_xo
 template <int BM, int BN, int WM, int WN, int R, int BK, bool CF = false>
 __global__ __launch_bounds__(256) void conv_fwd_k(ConvFwdArgs a) {
   constexpr int RS = R * R;
-  constexpr int LDK = BK + 4;
   constexpr int TM = BM / (WM * 16), TN = BN / (WN * 16);
   constexpr int TPR = 256 / BM;   // threads sharing one output row
   constexpr int KPT = BK / TPR;   // contraction steps each of them loads
   constexpr int QPR = BK / 4;     // float4 groups per B row
   constexpr int BQ = BN * QPR;
   constexpr int BPT = (BQ + 255) / 256;
-  __shared__ __attribute__((aligned(16))) float As[2][BM * LDK];
-  __shared__ __attribute__((aligned(16))) float Bs[2][BN * LDK];
+  __shared__ __attribute__((aligned(16))) v4f As[2][BM * BK / 4];
+  __shared__ __attribute__((aligned(16))) v4f Bs[2][BN * BK / 4];
 
   const ConvGeom g = a.g;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -200,14 +223,12 @@ __global__ __launch_bounds__(256) void conv_fwd_k(ConvFwdArgs a) {
   auto store = [&](int buf, const float (&ra)[KPT], const float (&rb)[BPT][4]) {
 #pragma unroll
     for (int q = 0; q < KPT / 4; ++q)
-      *reinterpret_cast<v4f*>(&As[buf][am * LDK + akq * KPT + 4 * q]) =
-          v4f{ra[4 * q], ra[4 * q + 1], ra[4 * q + 2], ra[4 * q + 3]};
+      As[buf][quad_at<BM>(am, akq * (KPT / 4) + q)] = v4f{ra[4 * q], ra[4 * q + 1], ra[4 * q + 2], ra[4 * q + 3]};
 #pragma unroll
     for (int u = 0; u < BPT; ++u) {
       const int idx = tid + u * 256;
       if (idx < BQ)
-        *reinterpret_cast<v4f*>(&Bs[buf][(idx / QPR) * LDK + 4 * (idx % QPR)]) =
-            v4f{rb[u][0], rb[u][1], rb[u][2], rb[u][3]};
+        Bs[buf][quad_at<BN>(idx / QPR, idx % QPR)] = v4f{rb[u][0], rb[u][1], rb[u][2], rb[u][3]};
     }
   };
 
@@ -228,7 +249,7 @@ __global__ __launch_bounds__(256) void conv_fwd_k(ConvFwdArgs a) {
       loadA((t + 1) * BK, ra);
       loadB((t + 1) * BK, rb);
     }
-    mma_stage<TM, TN, BK>(As[cur], Bs[cur], wm0, wn0, lane, acc);
+    mma_stage<BM, BN, TM, TN, BK>(As[cur], Bs[cur], wm0, wn0, lane, acc);
     if (t + 1 < T) store(cur ^ 1, ra, rb);
     __syncthreads();
   }
@@ -236,40 +257,47 @@ __global__ __launch_bounds__(256) void conv_fwd_k(ConvFwdArgs a) {
   const float* bias = a.bias ? a.bias + (int64_t)j * a.pstride : nullptr;
   float* Y = a.y + (int64_t)j * g.b * N * HoWo;
   const bool vec = (HoWo & 3) == 0 && (reinterpret_cast<uintptr_t>(Y) & 15) == 0;
+  int nn[TN];
+  float bv[TN];
   double s1[TN], s2[TN];  // per-column sums of the stored outputs (BN statistics)
 #pragma unroll
-  for (int y = 0; y < TN; ++y) s1[y] = s2[y] = 0.0;
+  for (int y = 0; y < TN; ++y) {
+    nn[y] = n0 + wn0 + y * 16 + (lane & 15);
+    bv[y] = bias && nn[y] < N ? bias[nn[y]] : 0.f;
+    s1[y] = s2[y] = 0.0;
+  }
+  int mb = m0 + wm0 + (lane >> 4) * 4;
+  RowIter it(mb, HoWo);
 #pragma unroll
-  for (int x = 0; x < TM; ++x)
+  for (int x = 0; x < TM; ++x, mb += 16, it.step16(HoWo)) {
+    float* Yx = Y + (int64_t)it.img * N * HoWo;
 #pragma unroll
     for (int y = 0; y < TN; ++y) {
-      const int n = n0 + wn0 + y * 16 + (lane & 15);
-      const int mb = m0 + wm0 + x * 16 + (lane >> 4) * 4;
-      if (n >= N || mb >= M) continue;
-      const float bv = bias ? bias[n] : 0.f;
-      int img = mb / HoWo, p = mb - img * HoWo;
+      v4f v = acc[x][y];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float e = v[i] + bv[y];
+        v[i] = a.relu ? relu0(e) : e;
+      }
+      if (nn[y] >= N || mb >= M) continue;
       if (vec) {
         // the lane's four pixels are consecutive in one plane
-        v4f v = acc[x][y];
+        if (a.stats)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          float e = v[i] + bv;
-          if (a.relu) e = relu0(e);
-          v[i] = e;
-          s1[y] += (double)e;
-          s2[y] += (double)e * e;
-        }
-        *reinterpret_cast<v4f*>(&Y[((int64_t)img * N + n) * HoWo + p]) = v;
+          for (int i = 0; i < 4; ++i) {
+            s1[y] += (double)v[i];
+            s2[y] += (double)v[i] * v[i];
+          }
+        *reinterpret_cast<v4f*>(&Yx[nn[y] * HoWo + it.p]) = v;
         continue;
       }
+      int img = it.img, p = it.p;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         if (mb + i < M) {
-          float v = acc[x][y][i] + bv;
-          if (a.relu) v = relu0(v);
-          Y[((int64_t)img * N + n) * HoWo + p] = v;
-          s1[y] += (double)v;
-          s2[y] += (double)v * v;
+          Y[((int64_t)img * N + nn[y]) * HoWo + p] = v[i];
+          s1[y] += (double)v[i];
+          s2[y] += (double)v[i] * v[i];
         }
         if (++p == HoWo) {
           p = 0;
@@ -277,6 +305,7 @@ __global__ __launch_bounds__(256) void conv_fwd_k(ConvFwdArgs a) {
         }
       }
     }
+  }
   if (!a.stats) return;
   // Per-channel partial sums of this tile for the batch norm that follows:
   // lanes with the same column combine by an xor butterfly, then the WM
@@ -323,15 +352,14 @@ __global__ __launch_bounds__(256) void conv_bwd_data_k(ConvBwdDataArgs a) {
   static_assert(!SP || (R == 1 && ST == 2), "the grid-only form is the 1x1 stride-2 case");
   static_assert(!CF || ST == 1 || SP, "the tap-major loaders read dY at stride 1");
   constexpr int RS = R * R;
-  constexpr int LDK = BK + 4;
   constexpr int TM = BM / (WM * 16), TN = BN / (WN * 16);
   constexpr int TPR = 256 / BM;
   constexpr int KPT = BK / TPR;
   constexpr int QPR = BK / 4;
   constexpr int BQ = BN * QPR;
   constexpr int BPT = (BQ + 255) / 256;
-  __shared__ __attribute__((aligned(16))) float As[2][BM * LDK];
-  __shared__ __attribute__((aligned(16))) float Bs[2][BN * LDK];
+  __shared__ __attribute__((aligned(16))) v4f As[2][BM * BK / 4];
+  __shared__ __attribute__((aligned(16))) v4f Bs[2][BN * BK / 4];
 
   const ConvGeom g = a.g;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -445,14 +473,12 @@ __global__ __launch_bounds__(256) void conv_bwd_data_k(ConvBwdDataArgs a) {
   auto store = [&](int buf, const float (&ra)[KPT], const float (&rb)[BPT][4]) {
 #pragma unroll
     for (int q = 0; q < KPT / 4; ++q)
-      *reinterpret_cast<v4f*>(&As[buf][am * LDK + akq * KPT + 4 * q]) =
-          v4f{ra[4 * q], ra[4 * q + 1], ra[4 * q + 2], ra[4 * q + 3]};
+      As[buf][quad_at<BM>(am, akq * (KPT / 4) + q)] = v4f{ra[4 * q], ra[4 * q + 1], ra[4 * q + 2], ra[4 * q + 3]};
 #pragma unroll
     for (int u = 0; u < BPT; ++u) {
       const int idx = tid + u * 256;
       if (idx < BQ)
-        *reinterpret_cast<v4f*>(&Bs[buf][(idx / QPR) * LDK + 4 * (idx % QPR)]) =
-            v4f{rb[u][0], rb[u][1], rb[u][2], rb[u][3]};
+        Bs[buf][quad_at<BN>(idx / QPR, idx % QPR)] = v4f{rb[u][0], rb[u][1], rb[u][2], rb[u][3]};
     }
   };
 
@@ -473,7 +499,7 @@ __global__ __launch_bounds__(256) void conv_bwd_data_k(ConvBwdDataArgs a) {
       loadA((t + 1) * BK, ra);
       loadB((t + 1) * BK, rb);
     }
-    mma_stage<TM, TN, BK>(As[cur], Bs[cur], wm0, wn0, lane, acc);
+    mma_stage<BM, BN, TM, TN, BK>(As[cur], Bs[cur], wm0, wn0, lane, acc);
     if (t + 1 < T) store(cur ^ 1, ra, rb);
     __syncthreads();
   }
@@ -504,6 +530,66 @@ __global__ __launch_bounds__(256) void conv_bwd_data_k(ConvBwdDataArgs a) {
   double s1[TN], s2[TN];
 #pragma unroll
   for (int y = 0; y < TN; ++y) s1[y] = s2[y] = 0.0;
+  if (!SP && vec && a.add_mode != ADD_SUBSAMPLE) {
+    // The lane's four pixels are consecutive in one plane: float4 access,
+    // the operands of a row of TN blocks read before any is used (blocks
+    // outside the tensor read element 0 and store nothing).  Reading all
+    // TM x TN blocks' first takes 220 registers, two waves per SIMD instead
+    // of four.
+    float bm[TN], bi[TN], bg[TN], bb[TN];
+#pragma unroll
+    for (int y = 0; y < TN; ++y) {
+      const int n = n0 + wn0 + y * 16 + (lane & 15), nn = n < N ? n : 0;
+      bm[y] = bn ? a.bn_mean[j * N + nn] : 0.f;
+      bi[y] = bn ? a.bn_istd[j * N + nn] : 0.f;
+      bg[y] = BG ? BG[nn] : 0.f;
+      bb[y] = BG ? BG[N + nn] : 0.f;
+    }
+    int mb = m0 + wm0 + (lane >> 4) * 4;
+    RowIter it(mb, HW);
+#pragma unroll
+    for (int x = 0; x < TM; ++x, mb += 16, it.step16(HW)) {
+      int64_t idx[TN];
+      bool ok[TN];
+      v4f old[TN], ad[TN], mk[TN], bx[TN], by[TN];
+#pragma unroll
+      for (int y = 0; y < TN; ++y) {
+        const int n = n0 + wn0 + y * 16 + (lane & 15);
+        ok[y] = n < N && mb < M;
+        idx[y] = ok[y] ? ((int64_t)it.img * N + n) * HW + it.p : 0;
+      }
+      auto read = [&](const float* t, v4f (&v)[TN]) {
+#pragma unroll
+        for (int y = 0; y < TN; ++y) v[y] = *reinterpret_cast<const v4f*>(t + idx[y]);
+      };
+      if (a.accumulate) read(DX, old);
+      if (a.add_mode == ADD_SAME) read(ADD, ad);
+      if (MSK) read(MSK, mk);
+      if (bn) read(BX, bx);
+      if (BY) read(BY, by);
+#pragma unroll
+      for (int y = 0; y < TN; ++y) {
+        v4f v = acc[x][y];
+        if (a.accumulate) v += old[y];
+        if (a.add_mode == ADD_SAME) v += ad[y];
+        if (MSK)
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (!(mk[y][i] > 0.f)) v[i] = 0.f;
+        if (!ok[y]) continue;
+        *reinterpret_cast<v4f*>(DX + idx[y]) = v;
+        if (!bn) continue;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const bool on = BY ? by[y][i] > 0.f : BG ? bn_affine(bx[y][i], bm[y], bi[y], bg[y], bb[y]) > 0.f : true;
+          const float d = on ? v[i] : 0.f;
+          const float xh = (bx[y][i] - bm[y]) * bi[y];
+          s1[y] += (double)d;
+          s2[y] += (double)d * xh;
+        }
+      }
+    }
+  } else {
 #pragma unroll
   for (int x = 0; x < TM; ++x)
 #pragma unroll
@@ -626,43 +712,6 @@ __global__ __launch_bounds__(256) void conv_bwd_data_k(ConvBwdDataArgs a) {
         }
         continue;
       }
-      if (vec) {
-        // the lane's four pixels are consecutive in one plane: float4 access
-        const int64_t idx = ((int64_t)img * N + n) * HW + p;
-        v4f v = acc[x][y];
-        if (a.accumulate) v += *reinterpret_cast<const v4f*>(DX + idx);
-        if (a.add_mode == ADD_SAME) {
-          v += *reinterpret_cast<const v4f*>(ADD + idx);
-        } else if (a.add_mode == ADD_SUBSAMPLE) {
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const int pp = p + i, ih = pp / g.W, iw = pp - ih * g.W;
-            if (ih % a.add_st == 0 && iw % a.add_st == 0)
-              v[i] += ADD[(((int64_t)img * a.add_C + n) * Hs + ih / a.add_st) * Ws + iw / a.add_st];
-          }
-        }
-        if (MSK) {
-          const v4f mk = *reinterpret_cast<const v4f*>(MSK + idx);
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-            if (!(mk[i] > 0.f)) v[i] = 0.f;
-        }
-        *reinterpret_cast<v4f*>(DX + idx) = v;
-        if (bn) {
-          const v4f bx = *reinterpret_cast<const v4f*>(BX + idx);
-          v4f by = {1.f, 1.f, 1.f, 1.f};
-          if (BY) by = *reinterpret_cast<const v4f*>(BY + idx);
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const bool on = BY ? by[i] > 0.f : BG ? bn_affine(bx[i], bm, bi, bg, bb) > 0.f : true;
-            const float d = on ? v[i] : 0.f;
-            const float xh = (bx[i] - bm) * bi;
-            s1[y] += (double)d;
-            s2[y] += (double)d * xh;
-          }
-        }
-        continue;
-      }
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         if (mb + i < M) {
@@ -692,6 +741,7 @@ __global__ __launch_bounds__(256) void conv_bwd_data_k(ConvBwdDataArgs a) {
         }
       }
     }
+  }
   if (!bn) return;
   // per-channel partial sums of this tile, combined in a fixed order (lanes
   // of a column by xor butterfly, then the WM waves of a column strip)
@@ -724,18 +774,26 @@ __global__ __launch_bounds__(256) void conv_bwd_data_k(ConvBwdDataArgs a) {
 }
 
 // ---------------------------------------------------------- weight grad
-// Stages of BK pixels; thread (pl, rg) loads pixel pl of the stage for the
-// dY rows rg, rg+RG, ... and the im2col rows (ci, r, s) rg, rg+RG, ...
-template <int BM, int BN, int WM, int WN, int R, int BK>
+// Stages of BK pixels.  QUADS (planes of a multiple of four pixels): thread
+// (q, rg) loads the four pixels of quad q for the dY rows rg, rg+RG, ... and
+// the im2col rows (ci, r, s) rg, rg+RG, ...; a quad never straddles two images
+// (splits start at multiples of BK), and dY is read four pixels at a time.
+// FLAT (1x1, stride 1, no padding): so is X, whose pixels are dY's.  Otherwise
+// a thread loads one pixel of four times as many rows.  The kernel is limited
+// by its loads: ResNet-50's flat layers (k=2 b=32) took 92 us per launch with
+// one pixel per load and take 73 with quads; its 7 x 7 layers measured slower
+// with four single loads per row (1x1 93 -> 135, 3x3 236 -> 289 us).
+template <int BM, int BN, int WM, int WN, int R, int BK, bool QUADS, bool FLAT>
 __global__ __launch_bounds__(256) void conv_bwd_weight_k(ConvBwdWeightArgs a) {
+  static_assert(!FLAT || (QUADS && R == 1), "flat X pixels are quads of a 1x1 layer");
   constexpr int RS = R * R;
-  constexpr int LDK = BK + 4;
   constexpr int TM = BM / (WM * 16), TN = BN / (WN * 16);
-  constexpr int RG = 256 / BK;            // row groups
-  constexpr int RA = BM / RG, RB = BN / RG;
-  static_assert(RA >= 1 && RB >= 1, "tile smaller than the row groups");
-  __shared__ __attribute__((aligned(16))) float As[2][BM * LDK];
-  __shared__ __attribute__((aligned(16))) float Bs[2][BN * LDK];
+  constexpr int PX = QUADS ? 4 : 1;       // pixels per thread and row
+  constexpr int RG = 256 / (BK / PX);     // row groups
+  constexpr int RA = (BM + RG - 1) / RG, RB = BN / RG;
+  static_assert(RB >= 1 && BN % RG == 0, "tile smaller than the row groups");
+  __shared__ __attribute__((aligned(16))) v4f As[2][BM * BK / 4];
+  __shared__ __attribute__((aligned(16))) v4f Bs[2][BN * BK / 4];
 
   const ConvGeom g = a.g;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -748,9 +806,10 @@ __global__ __launch_bounds__(256) void conv_bwd_weight_k(ConvBwdWeightArgs a) {
   const float* X = a.x + (int64_t)j * g.b * g.Ci * HW;
   const float* DY = a.dy + (int64_t)j * g.b * g.Co * HoWo;
 
-  const int pl = tid % BK, rg = tid / BK;
-  // pixel this thread loads in the current stage, kept as (img, oh, ow)
-  int pix = L0 + pl;
+  const int q4 = tid % (BK / PX), rg = tid / (BK / PX);
+  // first pixel this thread loads in the current stage, kept as
+  // (img, oh, ow)
+  int pix = L0 + PX * q4;
   int img = pix / HoWo, rem = pix - img * HoWo, oh = rem / g.Wo, ow = rem - oh * g.Wo;
   // (offset, r, s) of this thread's weight-gradient columns kk = (ci, r, s)
   int tx[RB], tr[RB], ts[RB];
@@ -762,24 +821,56 @@ __global__ __launch_bounds__(256) void conv_bwd_weight_k(ConvBwdWeightArgs a) {
     tr[i] = kk < No ? r : OUT_OF_RANGE;
     ts[i] = s;
   }
-  float ra[RA], rb[RB];
+  typedef float vpx __attribute__((ext_vector_type(PX)));
+  vpx ra[RA], rb[RB];
 
   auto load = [&]() {
-    const bool ok = pix < L1;
-    const int yb = img * g.Co * HoWo + oh * g.Wo + ow;
-    const int ih0 = oh * g.st - g.pad, iw0 = ow * g.st - g.pad;
-    const int xb = img * g.Ci * HW + ih0 * g.W + iw0;
+    if constexpr (QUADS) {
+      const bool ok = pix < L1;
+      const int p = oh * g.Wo + ow, yb = img * g.Co * HoWo + p, xb = img * g.Ci * HW + p;
 #pragma unroll
-    for (int i = 0; i < RA; ++i) {
-      const int co = m0 + rg + RG * i;
-      ra[i] = (ok && co < Mo) ? DY[yb + co * HoWo] : 0.f;
+      for (int i = 0; i < RA; ++i) {
+        const int co = m0 + rg + RG * i;
+        ra[i] = vpx(0.f);
+        if (ok && co < Mo) ra[i] = *reinterpret_cast<const vpx*>(DY + yb + co * HoWo);
+      }
+      if constexpr (FLAT) {
+#pragma unroll
+        for (int i = 0; i < RB; ++i) {
+          rb[i] = vpx(0.f);
+          if (ok && tr[i] == 0) rb[i] = *reinterpret_cast<const vpx*>(X + xb + tx[i]);
+        }
+        return;
+      }
     }
+    int pi = img, ph = oh, pw = ow;
 #pragma unroll
-    for (int i = 0; i < RB; ++i) {
-      float v = 0.f;
-      if (ok && (unsigned)(ih0 + tr[i]) < (unsigned)g.H && (unsigned)(iw0 + ts[i]) < (unsigned)g.W)
-        v = X[xb + tx[i]];
-      rb[i] = v;
+    for (int e = 0; e < PX; ++e) {
+      const bool ok = pix + e < L1;
+      if constexpr (!QUADS) {
+        const int yb = pi * g.Co * HoWo + ph * g.Wo + pw;
+#pragma unroll
+        for (int i = 0; i < RA; ++i) {
+          const int co = m0 + rg + RG * i;
+          ra[i][e] = ok && co < Mo ? DY[yb + co * HoWo] : 0.f;
+        }
+      }
+      const int ih0 = ph * g.st - g.pad, iw0 = pw * g.st - g.pad;
+      const int xb = pi * g.Ci * HW + ih0 * g.W + iw0;
+#pragma unroll
+      for (int i = 0; i < RB; ++i) {
+        float v = 0.f;
+        if (ok && (unsigned)(ih0 + tr[i]) < (unsigned)g.H && (unsigned)(iw0 + ts[i]) < (unsigned)g.W)
+          v = X[xb + tx[i]];
+        rb[i][e] = v;
+      }
+      if (++pw == g.Wo) {
+        pw = 0;
+        if (++ph == g.Ho) {
+          ph = 0;
+          ++pi;
+        }
+      }
     }
   };
   auto advance = [&]() {
@@ -793,11 +884,15 @@ __global__ __launch_bounds__(256) void conv_bwd_weight_k(ConvBwdWeightArgs a) {
       }
     }
   };
+  auto put = [&](v4f* quad, vpx v) {
+    reinterpret_cast<vpx*>(quad)[QUADS ? 0 : q4 & 3] = v;
+  };
   auto store = [&](int buf) {
 #pragma unroll
-    for (int i = 0; i < RA; ++i) As[buf][(rg + RG * i) * LDK + pl] = ra[i];
+    for (int i = 0; i < RA; ++i)
+      if (BM % RG == 0 || rg + RG * i < BM) put(&As[buf][quad_at<BM>(rg + RG * i, PX * q4 / 4)], ra[i]);
 #pragma unroll
-    for (int i = 0; i < RB; ++i) Bs[buf][(rg + RG * i) * LDK + pl] = rb[i];
+    for (int i = 0; i < RB; ++i) put(&Bs[buf][quad_at<BN>(rg + RG * i, PX * q4 / 4)], rb[i]);
   };
 
   v4f acc[TM][TN];
@@ -816,7 +911,7 @@ __global__ __launch_bounds__(256) void conv_bwd_weight_k(ConvBwdWeightArgs a) {
       advance();
       load();
     }
-    mma_stage<TM, TN, BK>(As[cur], Bs[cur], wm0, wn0, lane, acc);
+    mma_stage<BM, BN, TM, TN, BK>(As[cur], Bs[cur], wm0, wn0, lane, acc);
     if (t + 1 < T) store(cur ^ 1);
     __syncthreads();
   }
@@ -1078,9 +1173,11 @@ __global__ __launch_bounds__(256) void channel_sum_k(const float* dy, int b, int
 }
 
 inline unsigned cdiv(int64_t a, int64_t b) { return (unsigned)((a + b - 1) / b); }
+inline bool al16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
 // Name of one kernel instantiation, as the profiler shows its template.
-template <int KIND, int BM, int BN, int WM, int WN, int R, int ST, int BK>
+// (FORM 1: a weight gradient with dY in quads, 2: with X too).
+template <int KIND, int BM, int BN, int WM, int WN, int R, int ST, int BK, int FORM = 0>
 const char* tile_name() {
   // KIND 3: the grid-only data gradient (SP = true)
   static const char* base[4] = {"conv_fwd_k", "conv_bwd_data_k", "conv_bwd_weight_k",
@@ -1089,7 +1186,12 @@ const char* tile_name() {
                                std::to_string(BN) + ", " + std::to_string(WM) + ", " +
                                std::to_string(WN) + ", " + std::to_string(R) +
                                (ST ? ", " + std::to_string(ST) : "") + ", " +
-                               std::to_string(BK) + (KIND == 3 ? ", true>" : ">");
+                               std::to_string(BK) +
+                               (KIND == 3   ? ", true>"
+                                : KIND == 2 ? (FORM == 2   ? ", true, true>"
+                                               : FORM == 1 ? ", true, false>"
+                                                           : ", false, false>")
+                                            : ">");
   return n.c_str();
 }
 
@@ -1127,9 +1229,13 @@ hipError_t launch_bwd_data(const ConvBwdDataArgs& a, hipStream_t s, const char**
   constexpr int BK = stage_k<BM, SP>();
   const int M = SP ? a.g.b * a.g.Ho * a.g.Wo : a.g.b * a.g.H * a.g.W;
   dim3 grid(cdiv(M, BM), cdiv(a.g.Ci, BN), a.g.k);
+  // The grid-only form is bound by its epilogue's traffic, and more than two
+  // workgroups per CU slow it down (ResNet-50 k=2 b=32: 274 us per launch
+  // with two, 304 with three): unused LDS keeps its 50 KB tiles at two.
+  constexpr uint32_t shm = SP && BM == 128 && BN == 64 ? 8192 : 0;
   if constexpr (ST == 1 || SP) {
     if (a.g.Co % BK == 0) {
-      klaunch((conv_bwd_data_k<BM, BN, WM, WN, R, ST, BK, SP, true>), grid, dim3(256), 0, s, a);
+      klaunch((conv_bwd_data_k<BM, BN, WM, WN, R, ST, BK, SP, true>), grid, dim3(256), shm, s, a);
       if (name) {
         static const std::string n =
             std::string(SP ? tile_name<3, BM, BN, WM, WN, R, ST, BK>() : tile_name<1, BM, BN, WM, WN, R, ST, BK>()) +
@@ -1139,7 +1245,7 @@ hipError_t launch_bwd_data(const ConvBwdDataArgs& a, hipStream_t s, const char**
       return hipGetLastError();
     }
   }
-  klaunch((conv_bwd_data_k<BM, BN, WM, WN, R, ST, BK, SP>), grid, dim3(256), 0, s, a);
+  klaunch((conv_bwd_data_k<BM, BN, WM, WN, R, ST, BK, SP>), grid, dim3(256), shm, s, a);
   if (name) *name = SP ? tile_name<3, BM, BN, WM, WN, R, ST, BK>() : tile_name<1, BM, BN, WM, WN, R, ST, BK>();
   return hipGetLastError();
 }
@@ -1152,8 +1258,21 @@ template <int BM, int BN, int WM, int WN, int R>
 hipError_t launch_bwd_weight(const ConvBwdWeightArgs& a, hipStream_t s, const char** name) {
   constexpr int BK = BM >= 128 ? 16 : WG_BK;
   dim3 grid(cdiv(a.g.Co, BM), cdiv(a.g.Ci * R * R, BN), a.g.k * a.splits);
-  klaunch((conv_bwd_weight_k<BM, BN, WM, WN, R, BK>), grid, dim3(256), 0, s, a);
-  if (name) *name = tile_name<2, BM, BN, WM, WN, R, 0, BK>();
+  const bool quads = a.g.Ho * a.g.Wo % 4 == 0 && al16(a.dy);
+  if constexpr (R == 1) {
+    if (quads && a.g.st == 1 && a.g.pad == 0 && al16(a.x)) {
+      klaunch((conv_bwd_weight_k<BM, BN, WM, WN, R, BK, true, true>), grid, dim3(256), 0, s, a);
+      if (name) *name = tile_name<2, BM, BN, WM, WN, R, 0, BK, 2>();
+      return hipGetLastError();
+    }
+  }
+  if (quads) {
+    klaunch((conv_bwd_weight_k<BM, BN, WM, WN, R, BK, true, false>), grid, dim3(256), 0, s, a);
+    if (name) *name = tile_name<2, BM, BN, WM, WN, R, 0, BK, 1>();
+  } else {
+    klaunch((conv_bwd_weight_k<BM, BN, WM, WN, R, BK, false, false>), grid, dim3(256), 0, s, a);
+    if (name) *name = tile_name<2, BM, BN, WM, WN, R, 0, BK>();
+  }
   return hipGetLastError();
 }
 
@@ -1235,7 +1354,6 @@ hipError_t bwd_weight_r(const ConvBwdWeightArgs& a, hipStream_t s, const char** 
 
 }  // namespace
 
-inline bool al16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 inline bool al8(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 7) == 0; }
 
 int conv_fwd_tiles_m(const ConvGeom& g) {

@@ -642,3 +642,46 @@ def test_direct_conv_at_any_float_alignment(W, C):
         outs.append([t.cpu().numpy() for t in (y, st, dx, pt)])
     for a, c in zip(*outs):
         assert np.isfinite(a).all() and np.array_equal(a, c)
+
+
+# GEMM weight gradients read four pixels at a time (planes of a multiple of
+# four pixels) from dY, and from X where its pixels are dY's: replicas whose
+# pixels are not a multiple of the stage depth, ragged channels
+WGRAD_QUADS = [
+    ("quads.flat", 2, 3, 24, 6, 40, 1, 1, 0, 0, 1, 1),
+    ("quads.flat.wide", 1, 5, 70, 10, 130, 1, 1, 0, 1, 0, 1),
+    ("quads.1x1s2", 2, 3, 24, 12, 40, 1, 2, 0, 0, 0, 1),
+    ("quads.1x1pad", 1, 2, 20, 4, 36, 1, 1, 1, 0, 0, 1),
+    ("quads.3x3", 2, 3, 7, 6, 19, 3, 1, 1, 0, 0, 1),
+    ("quads.3x3.one", 1, 1, 5, 2, 6, 3, 1, 1, 0, 0, 1),
+    ("quads.7x7s2", 1, 2, 3, 20, 10, 7, 2, 3, 0, 0, 0),
+]
+
+
+@pytest.mark.parametrize("case", WGRAD_QUADS, ids=[c[0] for c in WGRAD_QUADS])
+def test_conv_weight_gradient_quads(case):
+    test_conv_kernels(case)
+
+
+@pytest.mark.parametrize("R,H,xo,dyo", [(1, 6, 1, 0), (1, 6, 0, 1), (3, 6, 1, 1)])
+def test_conv_weight_gradient_at_any_float_alignment(R, H, xo, dyo):
+    """The same sums whether or not X and dY allow 16-byte reads."""
+    L, k, b, Ci, Co, pad = cb.lib(), 2, 3, 24, 40, R // 2
+    src = [torch.randn(k * b * c * H * H, device="cuda",
+                       generator=torch.Generator(device="cuda").manual_seed(c)) for c in (Ci, Co)]
+    nw = Co * Ci * R * R
+    w, y = torch.zeros(k * nw, device="cuda"), torch.empty(k * b * Co * H * H, device="cuda")
+    scratch_n = L.cb_test_conv_scratch_bytes(k, b, Ci, H, H, Co, R, 1, pad)
+    scratch = torch.empty(scratch_n, dtype=torch.uint8, device="cuda")
+    outs = []
+    for offs in ((0, 0), (xo, dyo)):
+        x, dy = (torch.empty(t.numel() + 4, device="cuda")[o:o + t.numel()].copy_(t)
+                 for t, o in zip(src, offs))
+        gw = torch.full_like(w, float("nan"))
+        assert L.cb_test_conv(k, b, Ci, H, H, Co, R, 1, pad, 0, 0, x.data_ptr(), w.data_ptr(), nw,
+                              y.data_ptr(), None, dy.data_ptr(), None, gw.data_ptr(),
+                              scratch.data_ptr(), scratch_n,
+                              torch.cuda.current_stream().cuda_stream) == 0
+        torch.cuda.synchronize()
+        outs.append(gw.cpu().numpy())
+    assert np.isfinite(outs[0]).all() and np.array_equal(*outs)
