@@ -982,9 +982,10 @@ int enqueue_sma(cb_ctx* c, const float* G, int64_t gstride, int correct) {
   a.z = c->Z();
   a.zp = c->Zp();
   a.k = c->p.k;
-  a.P4 = (c->p.P + 3) / 4;  // stays inside a [k][P] gradient array when P % 4 == 0
+  a.P = c->p.P;
+  a.P4 = (c->p.P + 3) / 4;
   a.wstride4 = c->p.Pp / 4;
-  a.gstride4 = gstride / 4;
+  a.gstride = gstride;
   a.alpha = c->alpha;
   a.lr = c->lr;
   a.mu = c->mu;
@@ -1334,14 +1335,7 @@ int apply_grads(cb_ctx* c, const float* grads_dev, int correct) {
   if (rc) return rc;
   if (!grads_dev) return fail(c, CB_EINVAL, "grads is NULL");
   const Plan& p = c->p;
-  const bool aligned = p.P % 4 == 0 && reinterpret_cast<uintptr_t>(grads_dev) % 16 == 0;
-  if (aligned) {
-    rc = enqueue_sma(c, grads_dev, p.P, correct);
-  } else {
-    CB_HIP(c, hipMemcpy2DAsync(c->G(), (size_t)p.Pp * 4, grads_dev, (size_t)p.P * 4,
-                               (size_t)p.P * 4, p.k, hipMemcpyDeviceToDevice, c->stream));
-    rc = enqueue_sma(c, c->G(), p.Pp, correct);
-  }
+  rc = enqueue_sma(c, grads_dev, p.P, correct);
   if (rc) return rc;
   c->pending = false;
   if (correct && p.m.check_finite) return check_finite(c);

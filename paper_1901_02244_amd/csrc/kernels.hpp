@@ -362,8 +362,9 @@ struct SMAArgs {
   float* z;
   float* zp;
   int k;
-  int64_t P4;            // number of float4 columns
-  int64_t wstride4, gstride4;
+  int64_t P, P4;         // parameters, float4 columns (the last may be padded)
+  int64_t wstride4;      // W's and Wprev's rows, in float4s
+  int64_t gstride;       // G's rows, in floats (any alignment)
   float alpha, lr, mu, mu_l;
   int correct;           // 0: local step only (no correction, z untouched)
 };

@@ -233,6 +233,35 @@ def test_sma_kernel_matches_oracle(arch, k, mu_l):
     np.testing.assert_array_equal(ctx.cb_get_prev_central(), Zp2)
 
 
+@pytest.mark.parametrize("classes,off", [(c, o) for c in (10, 11, 12, 13) for o in (0, 1)])
+@pytest.mark.parametrize("k", [1, 3, 8])
+def test_sma_reads_caller_gradients_at_any_float_alignment(classes, off, k):
+    """Caller gradients [k][P] with every P % 4 (LeNet's P grows by 85 a
+    class), starting on and one float past a 16-byte boundary, NaNs around
+    them: the update matches the oracle's (same bar), and a local step after
+    it gives the same bytes from either start."""
+    m = cb.model("lenet5", 1, 28, 28, classes, learner_momentum=0.9)
+    P = cb.cb_num_params(m)
+    layout = cb.cb_tensor_layout(m)
+    W, G, Z, Zp = wl.random_state(k, P, seed=classes)
+    buf = torch.full((k * P + 8,), float("nan"), device="cuda")
+    g = buf[off:off + k * P].view(k, P).copy_(torch.from_numpy(G))
+    ctx = cb.Context(m, k, 1, 1.0 / k, 0.05, 0.9, Z)
+    ctx.cb_set_state(W, Z, Zp)
+    ctx.cb_sma_apply(g)
+    Wn, _, Zn, _ = oracle.sma_update(W, G, Z, Zp, f32(1.0 / k), f32(0.05), f32(0.9), f32(0.9))
+    _check_update(ctx, k, W, Z, Wn, Zn, layout, (classes, off))
+    ends = []
+    for o in (off, 4 - off):
+        buf.fill_(float("nan"))
+        g = buf[o:o + k * P].view(k, P).copy_(torch.from_numpy(G))
+        ctx.cb_set_state(W, Z, Zp)
+        ctx.cb_local_apply(g)
+        ends.append([ctx.cb_get_replica(j) for j in range(k)])
+    assert np.isfinite(ends).all()
+    np.testing.assert_array_equal(*ends)
+
+
 def test_sma_microbench_size_sampled():
     """The full SMA-only workload (ResNet-50's P, k = 32): the oracle
     computes 4096 sampled parameters (plus the first and last) one by one,
