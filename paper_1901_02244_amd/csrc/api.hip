@@ -873,6 +873,10 @@ int enqueue_step(cb_ctx* c, const float* x, const int32_t* labels, hipStream_t s
         a.parts = o.bwd_parts > 0 ? o.bwd_parts : o.chunks;
         const double n = (double)N * o.C * o.H * o.W;
         const double mask = a.y ? 1.0 : 0.0, dres = o.res >= 0 ? 1.0 : 0.0;
+        if (o.bwd_parts == 0 && bn_bwd_one_ok(a)) {
+          CB_LAUNCH(c, "bn_bwd_one_k", 0.0, 4.0 * n * (3.0 + mask + dres), bn_bwd_one(a, s));
+          break;
+        }
         if (o.bwd_parts == 0)
           CB_LAUNCH(c, "bn_bwd_stats_k", 0.0, 4.0 * n * (2.0 + mask), bn_bwd_stats(a, s));
         CB_LAUNCH(c, "bn_bwd_apply_k", 0.0, 4.0 * n * (3.0 + mask + dres), bn_bwd_apply(a, s, &nm_));

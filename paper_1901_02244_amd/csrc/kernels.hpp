@@ -280,6 +280,13 @@ hipError_t bn_fwd_apply(const BNArgs& a, hipStream_t s, const char** name = null
 hipError_t bn_bwd_stats(const BNBwdArgs& a, hipStream_t s);
 hipError_t bn_bwd_apply(const BNBwdArgs& a, hipStream_t s, const char** name = nullptr);
 
+// Sums and apply in one launch, where the shapes and pointers allow it (part
+// is not used; forward without a residual input).
+bool bn_fwd_one_ok(const BNArgs& a);
+hipError_t bn_fwd_one(const BNArgs& a, hipStream_t s);
+bool bn_bwd_one_ok(const BNBwdArgs& a);
+hipError_t bn_bwd_one(const BNBwdArgs& a, hipStream_t s);
+
 hipError_t maxpool_fwd(const float* x, int N, int C, int H, int W, int K, int st, int pad,
                        float* y, int Ho, int Wo, int* arg, hipStream_t s);
 // dx over the whole input; mask_relu zeroes entries whose input was <= 0.

@@ -9,6 +9,7 @@
 #include "kernels.hpp"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace cbk {
 namespace {
@@ -363,6 +364,202 @@ __global__ __launch_bounds__(256) void bn_bwd_apply_v4_k(BNBwdArgs a) {
     qb += BN_U * 256;
     if (qb >= q1) break;
     load();
+  }
+}
+
+// Both passes of a batch norm in one launch, a workgroup of NT threads per
+// (replica, channel): the first NK quads of each thread stay in registers
+// between the sums and the apply, the rest (and, backward, x) are read again
+// while the last-level cache still holds them.  The separate launches are
+// bound by memory and move each tensor twice; per-element arithmetic is
+// theirs, the fp64 sums group by thread.  ResNet-50's 56 x 56 stage, 256
+// channels, k = 2 b = 32: forward 140 -> 92 us, backward 218 -> 159 us, about
+// what one read and one write of each tensor take at 4.7 TB/s (87, 130).
+template <int NT>
+struct QuadIter {  // quads tid, tid + NT, ... of a (replica, channel)
+  int q, img, p4;
+  const int HW4, di, dp;
+  __device__ QuadIter(int tid, int HW4_) : q(tid), img(tid / HW4_), p4(tid - tid / HW4_ * HW4_),
+                                          HW4(HW4_), di(NT / HW4_), dp(NT - NT / HW4_ * HW4_) {}
+  __device__ void step() {
+    q += NT;
+    img += di;
+    p4 += dp;
+    if (p4 >= HW4) {
+      p4 -= HW4;
+      ++img;
+    }
+  }
+  // The same state, opaque to the compiler, which would otherwise keep every
+  // offset of the first pass in registers for the second.
+  __device__ void again() {
+    asm volatile("" : "+v"(q), "+v"(img), "+v"(p4));
+  }
+  // element offset of the quad from the (replica, channel) base (0 beyond n4)
+  __device__ int off(int n4, int CHW) const { return q < n4 ? img * CHW + 4 * p4 : 0; }
+};
+
+// Sum of two doubles over NT threads, fixed order; result in all threads.
+template <int NT>
+__device__ __forceinline__ void block_sum2_n(double& a, double& b, double (*red)[2]) {
+  a = wave_sum_d(a);
+  b = wave_sum_d(b);
+  if ((threadIdx.x & 63) == 0) {
+    red[threadIdx.x >> 6][0] = a;
+    red[threadIdx.x >> 6][1] = b;
+  }
+  __syncthreads();
+  a = red[0][0];
+  b = red[0][1];
+#pragma unroll
+  for (int w = 1; w < NT / 64; ++w) {
+    a += red[w][0];
+    b += red[w][1];
+  }
+}
+
+template <int NT, int NK>
+__global__ __launch_bounds__(NT) void bn_one_k(BNArgs a) {
+  __shared__ double red[NT / 64][2];
+  const int c = blockIdx.x, j = blockIdx.y;
+  const int HW = a.H * a.W, HW4 = HW >> 2, n4 = a.b * HW4, CHW = a.C * HW;
+  const int64_t base = ((int64_t)j * a.b * a.C + c) * HW;
+  const float* X = a.x + base;
+  v4f xv[NK];
+  QuadIter<NT> it(threadIdx.x, HW4);
+#pragma unroll
+  for (int u = 0; u < NK; ++u, it.step()) xv[u] = *reinterpret_cast<const v4f*>(X + it.off(n4, CHW));
+  double s = 0.0, ss = 0.0;
+  auto add = [&](v4f v) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      s += (double)v[i];
+      ss += (double)v[i] * v[i];
+    }
+  };
+#pragma unroll
+  for (int u = 0; u < NK; ++u)
+    if ((int)threadIdx.x + u * NT < n4) add(xv[u]);
+  for (; it.q < n4; it.step()) add(*reinterpret_cast<const v4f*>(X + it.off(n4, CHW)));
+  block_sum2_n<NT>(s, ss, red);
+  const int n = a.b * HW;
+  const double mean = s / n;
+  const double var = fmax(ss / n - mean * mean, 0.0);
+  const float mf = (float)mean, isf = (float)(1.0 / sqrt(var + BN_EPS));
+  if (threadIdx.x == 0) {
+    a.mean[j * a.C + c] = mf;
+    a.istd[j * a.C + c] = isf;
+  }
+  const float* gam = a.gamma + (int64_t)j * a.pstride;
+  const float ga = gam[c], be = gam[a.C + c];
+  auto apply = [&](v4f x, const QuadIter<NT>& q) {
+    const int64_t o = base + q.off(n4, CHW);
+    v4f v;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = bn_affine(x[i], mf, isf, ga, be);
+    if (a.relu)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[i] = v[i] > 0.f ? v[i] : 0.f;
+    *reinterpret_cast<v4f*>(a.y + o) = v;
+  };
+  QuadIter<NT> w(threadIdx.x, HW4);
+  w.again();
+#pragma unroll
+  for (int u = 0; u < NK; ++u, w.step())
+    if (w.q < n4) apply(xv[u], w);
+  for (; w.q < n4; w.step()) apply(*reinterpret_cast<const v4f*>(X + w.off(n4, CHW)), w);
+}
+
+template <int NT, int NK>
+__global__ __launch_bounds__(NT) void bn_bwd_one_k(BNBwdArgs a) {
+  __shared__ double red[NT / 64][2];
+  constexpr int U = 4;  // quads of x in flight
+  static_assert(NK % U == 0, "whole rounds");
+  const int c = blockIdx.x, j = blockIdx.y;
+  const int HW = a.H * a.W, HW4 = HW >> 2, n4 = a.b * HW4, CHW = a.C * HW;
+  const float mf = a.mean[j * a.C + c], isf = a.istd[j * a.C + c];
+  const float ga = a.gamma[(int64_t)j * a.pstride + c];
+  const float be = a.gamma[(int64_t)j * a.pstride + a.C + c];
+  const int64_t base = ((int64_t)j * a.b * a.C + c) * HW;
+  auto at = [&](const float* t, const QuadIter<NT>& q) {
+    return *reinterpret_cast<const v4f*>(t + base + q.off(n4, CHW));
+  };
+  // the gradient behind the ReLU
+  auto masked = [&](v4f d, v4f x, const QuadIter<NT>& q) {
+    if (a.y) {
+      const v4f y = at(a.y, q);
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (!(y[i] > 0.f)) d[i] = 0.f;
+    } else if (a.relu_x) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (!(bn_affine(x[i], mf, isf, ga, be) > 0.f)) d[i] = 0.f;
+    }
+    return d;
+  };
+  double s = 0.0, sx = 0.0;
+  auto add = [&](v4f d, v4f x) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      s += (double)d[i];
+      sx += (double)d[i] * ((x[i] - mf) * isf);
+    }
+  };
+  v4f dv[NK];
+  QuadIter<NT> it(threadIdx.x, HW4);
+#pragma unroll
+  for (int u0 = 0; u0 < NK; u0 += U) {
+    v4f xv[U];
+    QuadIter<NT> l = it;
+#pragma unroll
+    for (int u = 0; u < U; ++u, l.step()) {
+      dv[u0 + u] = at(a.dy, l);
+      xv[u] = at(a.x, l);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u, it.step()) {
+      dv[u0 + u] = masked(dv[u0 + u], xv[u], it);
+      if (it.q < n4) add(dv[u0 + u], xv[u]);
+    }
+  }
+  for (; it.q < n4; it.step()) {
+    const v4f x = at(a.x, it);
+    add(masked(at(a.dy, it), x, it), x);
+  }
+  block_sum2_n<NT>(s, sx, red);
+  const int n = a.b * HW;
+  if (threadIdx.x == 0) {
+    a.dgamma[(int64_t)j * a.pstride + c] = (float)sx;
+    a.dgamma[(int64_t)j * a.pstride + a.C + c] = (float)s;
+  }
+  const float k1 = ga * isf, mdy = (float)(s / n), mdyx = (float)(sx / n);
+  auto apply = [&](v4f d, v4f x, const QuadIter<NT>& q) {
+    v4f dx;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float xh = (x[i] - mf) * isf;
+      dx[i] = k1 * (d[i] - mdy - xh * mdyx);
+    }
+    const int64_t o = base + q.off(n4, CHW);
+    *reinterpret_cast<v4f*>(a.dx + o) = dx;
+    if (a.dres) *reinterpret_cast<v4f*>(a.dres + o) = d;
+  };
+  QuadIter<NT> w(threadIdx.x, HW4);
+  w.again();
+#pragma unroll
+  for (int u0 = 0; u0 < NK; u0 += U) {
+    v4f xv[U];
+    QuadIter<NT> l = w;
+#pragma unroll
+    for (int u = 0; u < U; ++u, l.step()) xv[u] = at(a.x, l);
+#pragma unroll
+    for (int u = 0; u < U; ++u, w.step())
+      if (w.q < n4) apply(dv[u0 + u], xv[u], w);
+  }
+  for (; w.q < n4; w.step()) {
+    const v4f x = at(a.x, w);
+    apply(masked(at(a.dy, w), x, w), x, w);
   }
 }
 
@@ -763,6 +960,67 @@ int bn_chunks(int b, int HW, int C, int k) {
   int chunks = (int)std::max<int64_t>(cdiv(512, (int64_t)C * k), n / 8192);
   chunks = std::min(chunks, (int)cdiv(n, 1024));
   return std::max(1, chunks);
+}
+
+namespace {
+
+// Whether the one-launch kernels take a batch norm: with one workgroup per
+// (replica, channel) against two launches over many, measured forward /
+// backward in us (one launch, then two):
+//   up to 4096 quads always: 1568 quads x 8 channels 4.5 / 5.1 against 6.7 / 6.9,
+//     3920 x 256 7.4 / 9.5 against 18.9 / 25.5
+//   more only with enough channels to occupy the chip: 8192 x 64 7.9 / 10.3
+//     against 10.3 / 11.8, but 8232 x 32 9.4 / 12.6 against 9.0 / 9.5;
+//     12544 x 64 12.3 / 17.2 against 13.7 / 16.7, x 128 13.8 / 19.4 against
+//     23.6 / 31.6; 25088 x 512 92 / 159 against 140 / 218
+//   far more than the registers hold: 100352 x 128 129 / 244 against 137 / 219,
+//     x 256 226 / 375 against 290 / 416
+bool bn_one_fits(int k, int b, int C, int HW) {
+  if (HW % 4) return false;
+  const int64_t n4 = (int64_t)b * (HW / 4), channels = (int64_t)k * C;
+  if (n4 <= 4096) return true;
+  return n4 <= 102400 && channels >= (n4 <= 8192 ? 64 : n4 <= 51200 ? 128 : 256);
+}
+
+// Threads and quads in registers by the quads of a (replica, channel): the
+// smallest workgroup that holds them all (6272 x 1024: 1024 threads 32 / 64 us,
+// 512 36 / 66, 256 42 / 71; 2800 x 288: 512 threads 7.4 / 9.7, 1024 9.7 / 13.9),
+// where many quads per thread leave fewer waves but idle fewer slots up to
+// 16384 (12544 x 800: 512 x 24 70 / 121, 1024 x 8 73 / 129, 1024 x 24 76 / 142)
+// and 1024 x 24 beyond (25088 x 512: 92 / 159, 1024 x 8 91 / 174).
+template <class F>
+void bn_one_pick(int b, int HW, const F& go) {
+  const int64_t n4 = (int64_t)b * (HW / 4);
+  if (n4 <= 256 * 8) go(std::integral_constant<int, 256>(), std::integral_constant<int, 8>());
+  else if (n4 <= 512 * 8) go(std::integral_constant<int, 512>(), std::integral_constant<int, 8>());
+  else if (n4 <= 1024 * 8) go(std::integral_constant<int, 1024>(), std::integral_constant<int, 8>());
+  else if (n4 <= 16384) go(std::integral_constant<int, 512>(), std::integral_constant<int, 24>());
+  else go(std::integral_constant<int, 1024>(), std::integral_constant<int, 24>());
+}
+
+}  // namespace
+
+bool bn_fwd_one_ok(const BNArgs& a) {
+  return bn_one_fits(a.k, a.b, a.C, a.H * a.W) && a.res_mode == RES_NONE && al16(a.x) && al16(a.y);
+}
+
+bool bn_bwd_one_ok(const BNBwdArgs& a) {
+  return bn_one_fits(a.k, a.b, a.C, a.H * a.W) && al16(a.x) && al16(a.y) && al16(a.dy) &&
+         al16(a.dx) && al16(a.dres);
+}
+
+hipError_t bn_fwd_one(const BNArgs& a, hipStream_t s) {
+  bn_one_pick(a.b, a.H * a.W, [&](auto nt, auto nk) {
+    klaunch((bn_one_k<nt.value, nk.value>), dim3(a.C, a.k), dim3(nt.value), 0, s, a);
+  });
+  return hipGetLastError();
+}
+
+hipError_t bn_bwd_one(const BNBwdArgs& a, hipStream_t s) {
+  bn_one_pick(a.b, a.H * a.W, [&](auto nt, auto nk) {
+    klaunch((bn_bwd_one_k<nt.value, nk.value>), dim3(a.C, a.k), dim3(nt.value), 0, s, a);
+  });
+  return hipGetLastError();
 }
 
 hipError_t bn_fwd_stats(const BNArgs& a, hipStream_t s) {

@@ -314,6 +314,29 @@ def test_batchnorm_backward_relu_mask_from_x(case):
         assert max_rel(g[j * pstride + C:j * pstride + 2 * C], dbo) <= TOL_STEP1, (name, j, "dbeta")
 
 
+# One launch per direction: each workgroup size at and past the quads it keeps
+# in registers, one image, one quad, and one quad more than each limit of the
+# rule (planes of 2 x 2 pixels: a quad an image)
+BN_ONE = [
+    ("one.quad", 1, 1, 3, 2, 1),
+    ("one.q256x8", 2, 2048, 3, 2, 1),
+    ("one.q512x8", 1, 2049, 2, 2, 0),
+    ("one.q4096", 1, 4096, 2, 2, 1),
+    ("one.over4096", 1, 4097, 2, 2, 1),
+    ("one.q1024x8", 1, 42, 64, 28, 0),
+    ("one.q512x24", 2, 12289, 64, 2, 1),
+    ("one.q1024x24", 1, 21, 128, 56, 1),
+    ("one.tail", 1, 25601, 128, 2, 1),
+]
+
+
+@pytest.mark.parametrize("case", BN_ONE, ids=[c[0] for c in BN_ONE])
+def test_batchnorm_one_launch(case):
+    test_batchnorm_kernels(case)
+    if case[-1]:
+        test_batchnorm_backward_relu_mask_from_x(case)
+
+
 # (name, N, C, H, W, K, stride, pad, mask_relu)
 POOL = [
     ("lenet.pool1", 128, 6, 28, 28, 2, 2, 0, 1),
