@@ -768,6 +768,131 @@ __global__ __launch_bounds__(256, 2) void conv3x3_flat_k(DirectArgs a) {
   }
 }
 
+// Weight gradient of the same layers at widths 14, 28 and 56, of 32 output
+// by 32 input channels and all nine taps per workgroup and split: stages of
+// SP consecutive pixels hold dY in quads and X in the flat kernel's padded
+// order, so a tap is a constant LDS offset and each value of X is staged
+// once for all taps, where the implicit GEMM gathers it nine times.  A wave
+// takes 16 x 16 channels, nine accumulators; every read of X feeds one
+// MFMA, 4 of whose 32 cycles the read occupies.  Splits, and the order of
+// the pixels within one (groups of 16, MFMA q taking pixels q, q + 4, ...),
+// are the GEMM's, so the sums are too, bit for bit.  Per launch (ResNet-50,
+// k = 2 b = 32; the GEMM takes 230 us for each): 14 wide 151 us (98 TFLOP/s), 28 164,
+// 56 176, where the halo of a stage is twice its pixels.
+template <int WW, int SP>
+__global__ __launch_bounds__(256, 2) void conv3x3_flat_wgrad_k(ConvBwdWeightArgs a) {
+  using S = DirectShape<WW, SP>;
+  constexpr int HW = S::HW, PW = S::PW, NP = S::NPIX;
+  constexpr int CS = (NP + 30) / 32 * 32 + 1;  // channel stride of X: 2-way bank conflicts at most
+  constexpr int NXC = (NP + 63) / 64;          // positions per lane
+  constexpr int Q = SP / 4, RG = 256 / Q, NA = 32 / RG;
+  static_assert(HW % 4 == 0 && SP % 16 == 0 && 256 % Q == 0 && 32 % RG == 0, "whole quads and rows");
+  constexpr int LDS = 32 * CS + 32 * SP > 4 * 16 * 144 ? 32 * CS + 32 * SP : 4 * 16 * 144;
+  __shared__ __attribute__((aligned(16))) float lds[LDS];
+  float* xs = lds;                                   // [input channel][padded pixel]
+  v4f* as = reinterpret_cast<v4f*>(lds + 32 * CS);   // [pixel quad][output channel]
+  auto quad = [](int q, int row) { return q * 32 + (row ^ ((0x84c0 >> (4 * (q & 3))) & 12)); };
+
+  const ConvGeom& g = a.g;
+  const int tid = threadIdx.x, lane = tid & 63, kq = lane >> 4, l16 = lane & 15;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wco = wave >> 1, wci = wave & 1;
+  // channel tiles of one replica and split are numbered together: they share
+  // dY and X in one XCD's L2
+  const int nci = g.Ci / 32, nco = g.Co / 32;
+  int t = xcd_major(blockIdx.x, gridDim.x);
+  const int ci0 = t % nci * 32;
+  t /= nci;
+  const int co0 = t % nco * 32;
+  t /= nco;
+  const int split = t % a.splits, j = t / a.splits;
+  const int L0 = split * a.chunk, L1 = min(g.b * HW, L0 + a.chunk);
+  const float* DY = a.dy + ((int64_t)j * g.b * g.Co + co0) * HW;
+
+  float rx[NXC][8];
+  v4f ra[NA];
+  auto load = [&](int m0) {
+    const int img0 = m0 / HW, v0 = S::corner(0, m0 - img0 * HW);
+    const auto src = buf_rsrc_u(a.x + ((int64_t)(j * g.b + img0) * g.Ci + ci0) * HW,
+                                (uint32_t)((min(g.b - img0, S::IMGS) * g.Ci - ci0) * HW) * 4u);
+#pragma unroll
+    for (int u = 0; u < NXC; ++u) {
+      const int e = lane + u * 64, v = v0 + e;
+      const int row = v / PW, iw = v - row * PW - 1, im = row / (WW + 1), ih = row - im * (WW + 1) - 1;
+      const bool ok = e < NP && ih >= 0 && iw >= 0 && img0 + im < g.b && im < S::IMGS;
+      const uint32_t xo = ok ? (uint32_t)(im * g.Ci * HW + ih * WW + iw) * 4u : OUTSIDE;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) rx[u][i] = buf_ld_s(src, xo, (uint32_t)((wave + 4 * i) * HW) * 4u);
+    }
+    const int m = m0 + 4 * (tid % Q), img = m / HW;
+    const bool ok = m < L1;  // the splits end at whole quads
+    const float* dy = DY + (ok ? ((int64_t)img * g.Co + tid / Q) * HW + m - img * HW : 0);
+#pragma unroll
+    for (int i = 0; i < NA; ++i) {
+      ra[i] = *reinterpret_cast<const v4a4*>(dy + (ok ? i * RG * HW : 0));
+      if (!ok) ra[i] = v4f{0.f, 0.f, 0.f, 0.f};
+    }
+  };
+  auto store = [&]() {
+#pragma unroll
+    for (int u = 0; u < NXC; ++u) {
+      const int e = lane + u * 64;
+      if (e < NP)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) xs[(wave + 4 * i) * CS + e] = rx[u][i];
+    }
+#pragma unroll
+    for (int i = 0; i < NA; ++i) as[quad(tid % Q, tid / Q + i * RG)] = ra[i];
+  };
+
+  v4f acc[9];
+#pragma unroll
+  for (int i = 0; i < 9; ++i) acc[i] = v4f{0.f, 0.f, 0.f, 0.f};
+  load(L0);
+  for (int m0 = L0; m0 < L1; m0 += SP) {
+    __syncthreads();  // the previous stage's reads are done
+    store();
+    __syncthreads();
+    if (m0 + SP < L1) load(m0 + SP);
+    const int img0 = m0 / HW, v0 = S::corner(0, m0 - img0 * HW);
+    const int ng = (min(L1 - m0, SP) + 15) / 16;
+#pragma unroll 1
+    for (int gr = 0; gr < ng; ++gr) {
+      const v4f av = as[quad(gr * 4 + kq, wco * 16 + l16)];
+      // padded position of the lane's four pixels (those past the last image
+      // fall on zeros)
+      const int m = m0 + gr * 16 + 4 * kq, img = m / HW, p = m - img * HW, ow = p % WW;
+      const float* xb = xs + (wci * 16 + l16) * CS + S::corner(img - img0, p) - v0;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const float* xq = xb + q + (ow + q >= WW ? 1 : 0);
+        float bv[9];
+#pragma unroll
+        for (int i = 0; i < 9; ++i) bv[i] = xq[(i / 3) * PW + i % 3];
+#pragma unroll
+        for (int i = 0; i < 9; ++i) acc[i] = mfma4(av[q], bv[i], acc[i]);
+      }
+    }
+  }
+
+  // acc[tap][r]: output channel co0 + 16 wco + 4 kq + r, input channel
+  // ci0 + 16 wci + l16; through LDS for rows of 288 consecutive values
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < 9; ++i)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) lds[(wave * 16 + 4 * kq + r) * 144 + l16 * 9 + i] = acc[i][r];
+  __syncthreads();
+  const int64_t wn = (int64_t)g.Co * g.Ci * 9;
+  float* out = a.splits == 1 ? a.dw + (int64_t)j * a.pstride
+                             : a.partial + (int64_t)(j * a.splits + split) * wn;
+  out += ((int64_t)co0 * g.Ci + ci0) * 9;
+  for (int e = tid; e < 32 * 288; e += 256) {
+    const int row = e / 288, c = e - row * 288;
+    out[(int64_t)row * g.Ci * 9 + c] =
+        lds[((row / 16 * 2 + c / 144) * 16 + row % 16) * 144 + c % 144];
+  }
+}
+
 // Data gradient of a 3x3, stride 2, pad 1 convolution, by output parity.
 // dX[ci][ih][iw] = sum over co and the taps (r, s) with ih + 1 - r and
 // iw + 1 - s even of W[co][ci][r][s] dY[co][(ih + 1 - r) / 2][(iw + 1 - s) / 2].
@@ -1201,6 +1326,18 @@ hipError_t launch_wgrad(const WgradArgs& a, hipStream_t s, const char** name) {
   return hipGetLastError();
 }
 
+template <int WW, int SP>
+hipError_t launch_flat_wgrad(const ConvBwdWeightArgs& a, hipStream_t s, const char** name) {
+  const dim3 grid((unsigned)((int64_t)(a.g.Co / 32) * (a.g.Ci / 32) * a.splits * a.g.k));
+  klaunch(conv3x3_flat_wgrad_k<WW, SP>, grid, dim3(256), 0, s, a);
+  if (name) {
+    static const std::string n = std::string("conv3x3_flat_wgrad_k<") + std::to_string(WW) + ", " +
+                                 std::to_string(SP) + ">";
+    *name = n.c_str();
+  }
+  return hipGetLastError();
+}
+
 template <int WO, int THO, int BN, int CC>
 hipError_t launch_s2(const DirectArgs& a, hipStream_t s, const char** name) {
   static int resident = 0;
@@ -1493,6 +1630,25 @@ hipError_t conv_direct_wgrad(const ConvBwdWeightArgs& w, hipStream_t s, const ch
   return launch_wgrad<8, WG_TH8, 1>(a, s, name);
 }
 
+
+// Flat weight gradient, on the splits (chunks of pixels) of the GEMM.  A
+// workgroup fills its pipeline once per split, so short splits stay on the
+// GEMM, whose tile is smaller: whole pass of one layer, us, GEMM then flat, at
+// 14 wide 64-pixel splits of 64 channels 23.8 / 28.3, 224 of 256 113.2 / 103.7;
+// at 28 wide 256 pixels 88.9 / 88.9, 352 101.7 / 100.9, 448 112.3 / 108.8; at 56
+// wide 224 67.2 / 69.7, 320 87.7 / 87.1, 576 124.4 / 121.2.
+bool conv_flat_wgrad_ok(const ConvGeom& g, int chunk) {
+  if (g.R != 3 || g.S != 3 || g.st != 1 || g.pad != 1 || g.H != g.W) return false;
+  if ((g.W != 14 && g.W != 28 && g.W != 56) || g.Ci % 32 || g.Co % 32) return false;
+  if ((int64_t)g.Ci * g.H * g.W * 16 >= OUTSIDE) return false;  // 32-bit offsets, as direct_ok
+  return chunk >= (g.W == 14 ? 224 : 384);
+}
+
+hipError_t conv_flat_wgrad(const ConvBwdWeightArgs& a, hipStream_t s, const char** name) {
+  if (a.g.W == 14) return launch_flat_wgrad<14, 128>(a, s, name);
+  if (a.g.W == 28) return launch_flat_wgrad<28, 128>(a, s, name);
+  return launch_flat_wgrad<56, 128>(a, s, name);
+}
 
 bool conv_direct_fwd_ok(const ConvGeom& g) {
   return direct_ok(g, false) || direct_s2_ok(g);

@@ -1488,6 +1488,7 @@ hipError_t conv_bwd_data(const ConvBwdDataArgs& a, hipStream_t s, const char** n
 hipError_t conv_bwd_weight(const ConvBwdWeightArgs& a, hipStream_t s, const char** name) {
   if (conv_direct_wgrad_ok(a.g))  // reads dY in 16-byte pieces
     return al16(a.dy) ? conv_direct_wgrad(a, s, name) : hipErrorInvalidValue;
+  if (conv_flat_wgrad_ok(a.g, a.chunk)) return conv_flat_wgrad(a, s, name);
   switch (a.g.R) {
     case 1: return bwd_weight_r<1>(a, s, name);
     case 3: return bwd_weight_r<3>(a, s, name);

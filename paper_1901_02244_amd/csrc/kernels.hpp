@@ -199,6 +199,10 @@ bool conv_direct_wgrad_ok(const ConvGeom& g);
 int conv_direct_wgrad_splits(const ConvGeom& g);
 hipError_t conv_direct_wgrad(const ConvBwdWeightArgs& a, hipStream_t s,
                              const char** name = nullptr);
+// The weight gradient of the wider 3x3 stride-1 layers (conv_bwd_weight
+// routes; the GEMM's splits of `chunk` pixels).
+bool conv_flat_wgrad_ok(const ConvGeom& g, int chunk);
+hipError_t conv_flat_wgrad(const ConvBwdWeightArgs& a, hipStream_t s, const char** name = nullptr);
 hipError_t conv_direct_fwd(const ConvFwdArgs& a, hipStream_t s, const char** name = nullptr);
 hipError_t conv_direct_bwd_data(const ConvBwdDataArgs& a, hipStream_t s,
                                 const char** name = nullptr);

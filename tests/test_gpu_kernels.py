@@ -708,3 +708,21 @@ def test_conv_weight_gradient_at_any_float_alignment(R, H, xo, dyo):
         torch.cuda.synchronize()
         outs.append(gw.cpu().numpy())
     assert np.isfinite(outs[0]).all() and np.array_equal(*outs)
+
+
+# the flat weight gradient: splits whose last stage is partial, a last split
+# and a last quad group that are partial, stages that span images, one split
+WGRAD_FLAT = [
+    ("wgflat.w14", 1, 27, 96, 14, 160, 3, 1, 1, 0, 0, 0),
+    ("wgflat.w14.one.split", 32, 1, 128, 14, 128, 3, 1, 1, 0, 1, 0),
+    ("wgflat.w14.ragged", 3, 9, 32, 14, 416, 3, 1, 1, 0, 0, 0),
+    ("wgflat.w28", 32, 4, 32, 28, 32, 3, 1, 1, 0, 0, 0),
+    ("wgflat.w28.ragged", 8, 3, 96, 28, 64, 3, 1, 1, 0, 0, 0),
+    ("wgflat.w56", 32, 1, 32, 56, 32, 3, 1, 1, 0, 1, 0),
+    ("wgflat.w56.b2", 6, 2, 64, 56, 96, 3, 1, 1, 0, 0, 0),
+]
+
+
+@pytest.mark.parametrize("case", WGRAD_FLAT, ids=[c[0] for c in WGRAD_FLAT])
+def test_conv_weight_gradient_flat(case):
+    test_conv_kernels(case)
