@@ -344,11 +344,18 @@ __global__ __launch_bounds__(256) void conv_fwd_k(ConvFwdArgs a) {
 // MFMA work) and the epilogue writes the 2x2 block of each grid point: the
 // contraction at (2oh, 2ow), zero at the other three, every pixel through
 // the same accumulate / add / mask / batch-norm epilogue.
-// CF (stride 1 or the grid-only form, Co a multiple of BK): the contraction
-// runs over k = (channel block, r, s, co in the block), as in the forward
-// kernel.
-template <int BM, int BN, int WM, int WN, int R, int ST, int BK, bool SP = false, bool CF = false>
+// LD TAPS (stride 1 or the grid-only form, Co a multiple of BK): the
+// contraction runs over k = (channel block, r, s, co in the block), as in the
+// forward kernel.  LD BUF: over (co, r, s), without branches either: a tap's
+// window check is a bit of a mask, its offset wave-uniform (at stride 2 too,
+// where a tap reads dY only from pixels of its parity), every element a
+// buffer load.  LD PLAIN: the same order by pointer, for tensors past the
+// 32-bit offsets of a buffer.
+enum GradLoad { PLAIN, TAPS, BUF };
+
+template <int BM, int BN, int WM, int WN, int R, int ST, int BK, bool SP, int LD>
 __global__ __launch_bounds__(256) void conv_bwd_data_k(ConvBwdDataArgs a) {
+  constexpr bool CF = LD == TAPS;
   static_assert(!SP || (R == 1 && ST == 2), "the grid-only form is the 1x1 stride-2 case");
   static_assert(!CF || ST == 1 || SP, "the tap-major loaders read dY at stride 1");
   constexpr int RS = R * R;
@@ -391,22 +398,23 @@ __global__ __launch_bounds__(256) void conv_bwd_data_k(ConvBwdDataArgs a) {
   }
   float ra[KPT];
   float rb[BPT][4];
-  // tap-major loaders: the lane's dY window as row and column masks (tap
-  // (r, s) reads dY row thp - r, column twp - s), every load a buffer load
-  // that reads 0 at OUTSIDE
+  // buffer loaders: the lane's dY window as row and column masks (tap
+  // (r, s) reads dY row (thp - r) / ST, column (twp - s) / ST where they are
+  // whole), every load a buffer load that reads 0 at OUTSIDE
   uint32_t rmask = 0, cmask = 0;
   int ybase = 0;
-  if (CF && m0 + am < M) {
+  if (LD != PLAIN && m0 + am < M) {
     if (SP) {
       rmask = cmask = 1u;
       ybase = yb;
     } else {
 #pragma unroll
       for (int r = 0; r < R; ++r) {
-        if ((unsigned)(thp - r) < (unsigned)g.Ho) rmask |= 1u << r;
-        if ((unsigned)(twp - r) < (unsigned)g.Wo) cmask |= 1u << r;
+        if ((unsigned)(thp - r) < (unsigned)(ST * g.Ho) && (thp - r) % ST == 0) rmask |= 1u << r;
+        if ((unsigned)(twp - r) < (unsigned)(ST * g.Wo) && (twp - r) % ST == 0) cmask |= 1u << r;
       }
-      ybase = yb + thp * g.Wo + twp;
+      // (thp - r) / ST = thp / ST - r / ST where thp - r is a multiple of ST
+      ybase = yb + thp / ST * g.Wo + twp / ST;
     }
   }
   const uint32_t dybytes = (uint32_t)((int64_t)g.b * g.Co * HoWo * 4);
@@ -421,6 +429,18 @@ __global__ __launch_bounds__(256) void conv_bwd_data_k(ConvBwdDataArgs a) {
       const uint32_t a0 = in ? (uint32_t)(ybase + c0 * HoWo - r * g.Wo - s) * 4u : OUTSIDE;
 #pragma unroll
       for (int i = 0; i < KPT; ++i) ra[i] = buf_ld(ysrc, a0 + (uint32_t)(i * HoWo) * 4u);
+      return;
+    }
+    if constexpr (LD == BUF) {
+      const auto ysrc = buf_rsrc_u(DY, dybytes);
+#pragma unroll
+      for (int i = 0; i < KPT; ++i) {
+        const int k = k0 + akq * KPT + i;  // wave-uniform
+        const int co = k / RS, rs = k - co * RS, r = rs / R, s = rs - r * R;
+        const int koff = __builtin_amdgcn_readfirstlane(co * HoWo - r / ST * g.Wo - s / ST);
+        const uint32_t in = (rmask >> r) & (cmask >> s) & (k < K ? 1u : 0u);
+        ra[i] = buf_ld(ysrc, (in & 1u) ? (uint32_t)(ybase + koff) * 4u : OUTSIDE);
+      }
       return;
     }
 #pragma unroll
@@ -455,6 +475,19 @@ __global__ __launch_bounds__(256) void conv_bwd_data_k(ConvBwdDataArgs a) {
         const uint32_t b0 = idx < BQ && n < N ? (uint32_t)((co * N + n) * RS + rs) * 4u : OUTSIDE;
 #pragma unroll
         for (int i = 0; i < 4; ++i) rb[u][i] = buf_ld(wsrc, b0 + (uint32_t)(i * N * RS) * 4u);
+      }
+      return;
+    }
+    if constexpr (LD == BUF) {
+      const auto wsrc = buf_rsrc_u(Wt, wbytes);
+#pragma unroll
+      for (int u = 0; u < BPT; ++u) {
+        const int idx = tid + u * 256, n = n0 + idx / QPR, kq = k0 + 4 * (idx % QPR);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int k = kq + i, co = k / RS, rs = k - co * RS;
+          rb[u][i] = buf_ld(wsrc, idx < BQ && n < N && k < K ? (uint32_t)((co * N + n) * RS + rs) * 4u : OUTSIDE);
+        }
       }
       return;
     }
@@ -1235,7 +1268,7 @@ hipError_t launch_bwd_data(const ConvBwdDataArgs& a, hipStream_t s, const char**
   constexpr uint32_t shm = SP && BM == 128 && BN == 64 ? 8192 : 0;
   if constexpr (ST == 1 || SP) {
     if (a.g.Co % BK == 0) {
-      klaunch((conv_bwd_data_k<BM, BN, WM, WN, R, ST, BK, SP, true>), grid, dim3(256), shm, s, a);
+      klaunch((conv_bwd_data_k<BM, BN, WM, WN, R, ST, BK, SP, TAPS>), grid, dim3(256), shm, s, a);
       if (name) {
         static const std::string n =
             std::string(SP ? tile_name<3, BM, BN, WM, WN, R, ST, BK>() : tile_name<1, BM, BN, WM, WN, R, ST, BK>()) +
@@ -1245,7 +1278,11 @@ hipError_t launch_bwd_data(const ConvBwdDataArgs& a, hipStream_t s, const char**
       return hipGetLastError();
     }
   }
-  klaunch((conv_bwd_data_k<BM, BN, WM, WN, R, ST, BK, SP>), grid, dim3(256), shm, s, a);
+  const ConvGeom& g = a.g;
+  if ((int64_t)g.b * g.Co * g.Ho * g.Wo * 4 < OUTSIDE && (int64_t)g.Co * g.Ci * R * R * 4 < OUTSIDE)
+    klaunch((conv_bwd_data_k<BM, BN, WM, WN, R, ST, BK, SP, BUF>), grid, dim3(256), shm, s, a);
+  else
+    klaunch((conv_bwd_data_k<BM, BN, WM, WN, R, ST, BK, SP, PLAIN>), grid, dim3(256), shm, s, a);
   if (name) *name = SP ? tile_name<3, BM, BN, WM, WN, R, ST, BK>() : tile_name<1, BM, BN, WM, WN, R, ST, BK>();
   return hipGetLastError();
 }

@@ -726,3 +726,24 @@ WGRAD_FLAT = [
 @pytest.mark.parametrize("case", WGRAD_FLAT, ids=[c[0] for c in WGRAD_FLAT])
 def test_conv_weight_gradient_flat(case):
     test_conv_kernels(case)
+
+
+# GEMM data gradients by masked buffer loads in the order (co, r, s): strides,
+# odd and even planes, no padding, one tap row past the last output, channel
+# counts that leave part of a stage, every column tile
+DGRAD_BUF = [
+    ("buf.3x3s2.odd", 3, 5, 52, 45, 74, 3, 2, 1, 1, 1, 1),
+    ("buf.3x3s2.even", 2, 3, 20, 12, 33, 3, 2, 1, 0, 0, 1),
+    ("buf.3x3s2.pad0", 2, 3, 9, 10, 16, 3, 2, 0, 0, 0, 1),
+    ("buf.3x3s2.one", 1, 1, 1, 3, 1, 3, 2, 1, 0, 0, 1),
+    ("buf.1x1s2.grid", 2, 3, 70, 8, 45, 1, 2, 0, 0, 0, 1),
+    ("buf.1x1s2.odd", 2, 3, 34, 7, 32, 1, 2, 0, 0, 0, 1),
+    ("buf.5x5.pad0", 2, 2, 17, 9, 21, 5, 1, 0, 0, 0, 1),
+    ("buf.3x3.wide", 4, 9, 130, 11, 23, 3, 1, 1, 0, 0, 1),
+    ("buf.1x1pad", 1, 2, 20, 5, 37, 1, 1, 1, 0, 0, 1),
+]
+
+
+@pytest.mark.parametrize("case", DGRAD_BUF, ids=[c[0] for c in DGRAD_BUF])
+def test_conv_data_gradient_buffer_loads(case):
+    test_conv_kernels(case)
