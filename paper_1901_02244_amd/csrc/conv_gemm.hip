@@ -1257,6 +1257,9 @@ hipError_t launch_fwd(const ConvFwdArgs& a, hipStream_t s, const char** name) {
   return hipGetLastError();
 }
 
+// Enough workgroups to give every CU at least two.
+constexpr int64_t MIN_WGS = 512;
+
 template <int BM, int BN, int WM, int WN, int R, int ST, bool SP = false>
 hipError_t launch_bwd_data(const ConvBwdDataArgs& a, hipStream_t s, const char** name) {
   constexpr int BK = stage_k<BM, SP>();
@@ -1278,8 +1281,13 @@ hipError_t launch_bwd_data(const ConvBwdDataArgs& a, hipStream_t s, const char**
       return hipGetLastError();
     }
   }
+  // 5x5 layers with less than a workgroup per CU stay on the pointer loads,
+  // which skip what the window leaves out (882 -> 12 channels, 13x13, 14
+  // workgroups: the whole layer 951 us, by buffer 1032; with 2800 workgroups,
+  // 88 -> 3 channels, 106x106, 2595 and 2457).
   const ConvGeom& g = a.g;
-  if ((int64_t)g.b * g.Co * g.Ho * g.Wo * 4 < OUTSIDE && (int64_t)g.Co * g.Ci * R * R * 4 < OUTSIDE)
+  const bool few = R == 5 && (int64_t)grid.x * grid.y * grid.z < MIN_WGS / 2;
+  if (!few && (int64_t)g.b * g.Co * g.Ho * g.Wo * 4 < OUTSIDE && (int64_t)g.Co * g.Ci * R * R * 4 < OUTSIDE)
     klaunch((conv_bwd_data_k<BM, BN, WM, WN, R, ST, BK, SP, BUF>), grid, dim3(256), shm, s, a);
   else
     klaunch((conv_bwd_data_k<BM, BN, WM, WN, R, ST, BK, SP, PLAIN>), grid, dim3(256), shm, s, a);
@@ -1303,13 +1311,19 @@ hipError_t launch_bwd_weight(const ConvBwdWeightArgs& a, hipStream_t s, const ch
       return hipGetLastError();
     }
   }
-  if (quads) {
-    klaunch((conv_bwd_weight_k<BM, BN, WM, WN, R, BK, true, false>), grid, dim3(256), 0, s, a);
-    if (name) *name = tile_name<2, BM, BN, WM, WN, R, 0, BK, 1>();
-  } else {
-    klaunch((conv_bwd_weight_k<BM, BN, WM, WN, R, BK, false, false>), grid, dim3(256), 0, s, a);
-    if (name) *name = tile_name<2, BM, BN, WM, WN, R, 0, BK>();
+  // With dY's quads alone, X's single pixels lie four lanes apart: that pays
+  // where dY has as many rows as X (64: 3x3 235 -> 230 us) but not where it
+  // has few (16 channels of 84x84, k=2 b=37, forward and weight gradient:
+  // 117 us by pixels, 129 by quads).
+  if constexpr (BM >= 64) {
+    if (quads) {
+      klaunch((conv_bwd_weight_k<BM, BN, WM, WN, R, BK, true, false>), grid, dim3(256), 0, s, a);
+      if (name) *name = tile_name<2, BM, BN, WM, WN, R, 0, BK, 1>();
+      return hipGetLastError();
+    }
   }
+  klaunch((conv_bwd_weight_k<BM, BN, WM, WN, R, BK, false, false>), grid, dim3(256), 0, s, a);
+  if (name) *name = tile_name<2, BM, BN, WM, WN, R, 0, BK>();
   return hipGetLastError();
 }
 
@@ -1320,9 +1334,6 @@ hipError_t launch_bwd_weight(const ConvBwdWeightArgs& a, hipStream_t s, const ch
 int bwd_weight_bm(int Co, int R) {
   return Co <= 16 ? 16 : (Co <= 32 ? 32 : (Co < 128 || R > 1 ? 64 : 128));
 }
-
-// Enough workgroups to give every CU at least two.
-constexpr int64_t MIN_WGS = 512;
 
 // Output-tile choice for the forward / data-gradient GEMM (M x N per
 // replica): the biggest tile of the N class that still yields MIN_WGS

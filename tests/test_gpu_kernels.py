@@ -676,6 +676,7 @@ WGRAD_QUADS = [
     ("quads.1x1s2", 2, 3, 24, 12, 40, 1, 2, 0, 0, 0, 1),
     ("quads.1x1pad", 1, 2, 20, 4, 36, 1, 1, 1, 0, 0, 1),
     ("quads.3x3", 2, 3, 7, 6, 19, 3, 1, 1, 0, 0, 1),
+    ("quads.3x3.rows64", 2, 3, 7, 6, 45, 3, 1, 1, 0, 0, 1),
     ("quads.3x3.one", 1, 1, 5, 2, 6, 3, 1, 1, 0, 0, 1),
     ("quads.7x7s2", 1, 2, 3, 20, 10, 7, 2, 3, 0, 0, 0),
 ]
