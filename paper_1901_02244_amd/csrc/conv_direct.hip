@@ -559,12 +559,18 @@ __global__ __launch_bounds__(256, 2) void conv3x3_flat_k(DirectArgs a) {
     }
   };
 
-  // The contraction runs over (chunk, tap, q), the order of the implicit
-  // GEMM's tap-major loaders with 16-step stages.
+  // The contraction runs over (chunk, tap, q) in the order of the kernel that
+  // this one stands in for, so a layer's sums do not depend on which of the
+  // two its size picks: window positions 0..8 as conv3x3_k at widths 8 and
+  // 16, filter taps 0..8 as the implicit GEMM's tap-major loaders with 16-step
+  // stages at the others (in the data gradient window position i meets
+  // filter tap 8 - i).
+  constexpr bool TAPS_DOWN = FLIP && WW != 8 && WW != 16;
   v4f acc[TN][TM];
   auto multiply = [&]() {
 #pragma unroll
-    for (int tap = 0; tap < 9; ++tap) {
+    for (int step = 0; step < 9; ++step) {
+      const int tap = TAPS_DOWN ? 8 - step : step;
       v4f av[TM], bv[TN];
 #pragma unroll
       for (int x = 0; x < TM; ++x) av[x] = xs[xb[x] + (tap / 3) * PW + tap % 3];

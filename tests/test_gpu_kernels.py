@@ -631,6 +631,34 @@ def test_conv_flat_tiles(case):
     (test_conv_kernels if len(case) == 12 else test_conv_data_gradient_epilogue)(case)
 
 
+# (W, channels, k, b, dX at an inner pixel): flat data gradients and, with fewer
+# learners or images, the kernels they stand in for
+TAP_ORDER = [(7, 704, 3, 9, 0), (7, 704, 1, 1, 0), (14, 512, 2, 5, 0), (14, 512, 1, 1, 0),
+             (28, 448, 1, 3, 0), (28, 64, 1, 1, 0), (56, 64, 1, 1, 0),
+             (8, 256, 2, 31, 1), (8, 16, 1, 1, 1), (16, 512, 2, 8, 1), (16, 16, 1, 1, 1)]
+
+
+@pytest.mark.parametrize("W,C,k,b,want", TAP_ORDER)
+def test_conv_data_gradient_tap_order(W, C, k, b, want):
+    """The order in which a 3x3 data gradient adds its nine taps, which a flat
+    tile keeps from the kernel it stands in for: with taps 0, 1, 2 of one
+    channel 2^24, 1, -2^24 and the others 0, fp32 gives 0 from tap 0 up and 1
+    from tap 8 down."""
+    Co, n = 16, k * b
+    w = np.zeros((k, Co, C, 9), dtype=np.float32)
+    w[:, 5, :, :3] = 2.0 ** 24, 1.0, -2.0 ** 24
+    dy = np.zeros((n, Co, W, W), dtype=np.float32)
+    dy[:, 5] = 1.0
+    wd, dyd = _dev(w), _dev(dy)
+    dx = torch.full((n, C, W, W), float("nan"), device="cuda")
+    assert cb.lib().cb_test_conv_dgrad(k, b, C, W, W, Co, 3, 1, 1, dyd.data_ptr(), wd.data_ptr(),
+                                       Co * C * 9, dx.data_ptr(), 0, None, None, 0, 0, None, None,
+                                       None, None, None, None,
+                                       torch.cuda.current_stream().cuda_stream) == 0
+    torch.cuda.synchronize()
+    assert (dx[:, :, 1:-1, 1:-1] == want).all()
+
+
 @pytest.mark.parametrize("W,C", [(14, 512), (16, 32), (32, 16)])
 def test_direct_conv_at_any_float_alignment(W, C):
     """The stride-1 direct kernels move four floats at a time at any float's
