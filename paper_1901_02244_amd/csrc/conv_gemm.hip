@@ -24,6 +24,7 @@
 
 #include <algorithm>
 #include <string>
+#include <type_traits>
 
 namespace cbk {
 namespace {
@@ -351,13 +352,25 @@ __global__ __launch_bounds__(256) void conv_fwd_k(ConvFwdArgs a) {
 // where a tap reads dY only from pixels of its parity), every element a
 // buffer load.  LD PLAIN: the same order by pointer, for tensors past the
 // 32-bit offsets of a buffer.
+// VEC: a float4 epilogue (planes of a multiple of four pixels, 16-byte
+// aligned tensors) that reads a row's operands ahead.  It is a kernel of its
+// own because it needs more registers than the scalar one: with both in one
+// kernel every layer ran at three waves per SIMD instead of four or five.
+// Data gradient with mask, shortcut and batch-norm sums, both epilogues in
+// one kernel -> two: 7x7, 2048 -> 512 channels 1x1, k=2 b=32 290 -> 260 us; 75x75,
+// 384 -> 16 1x1 stride 2, k=3 b=1 206 -> 188 us.  At 128 rows the launch bounds
+// hold the float4 form to the scalar form's four (five at 32 columns) waves:
+// 20x20, 512 -> 128 1x1, k=2 b=16 53 -> 48 us; ResNet-50 k=2 b=32 23.05 -> 22.87 ms a
+// step.  A subsampled shortcut is added here too (98x98, 128 -> 16 3x3 stride 2,
+// k=3 b=48: 1337 us, through the scalar epilogue 3204).
 enum GradLoad { PLAIN, TAPS, BUF };
 
-template <int BM, int BN, int WM, int WN, int R, int ST, int BK, bool SP, int LD>
-__global__ __launch_bounds__(256) void conv_bwd_data_k(ConvBwdDataArgs a) {
+template <int BM, int BN, int WM, int WN, int R, int ST, int BK, bool SP, int LD, bool VEC>
+__global__ __launch_bounds__(256, VEC && BM == 128 ? (BN == 64 ? 4 : 5) : 1) void conv_bwd_data_k(ConvBwdDataArgs a) {
   constexpr bool CF = LD == TAPS;
   static_assert(!SP || (R == 1 && ST == 2), "the grid-only form is the 1x1 stride-2 case");
   static_assert(!CF || ST == 1 || SP, "the tap-major loaders read dY at stride 1");
+  static_assert(!SP || !VEC, "the grid-only form has its own float4 epilogue");
   constexpr int RS = R * R;
   constexpr int TM = BM / (WM * 16), TN = BN / (WN * 16);
   constexpr int TPR = 256 / BM;
@@ -483,10 +496,12 @@ __global__ __launch_bounds__(256) void conv_bwd_data_k(ConvBwdDataArgs a) {
 #pragma unroll
       for (int u = 0; u < BPT; ++u) {
         const int idx = tid + u * 256, n = n0 + idx / QPR, kq = k0 + 4 * (idx % QPR);
+        const bool row = (idx < BQ) & (n < N);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const int k = kq + i, co = k / RS, rs = k - co * RS;
-          rb[u][i] = buf_ld(wsrc, idx < BQ && n < N && k < K ? (uint32_t)((co * N + n) * RS + rs) * 4u : OUTSIDE);
+          // no && here: the compiler branches on it and then waits for loads in flight
+          rb[u][i] = buf_ld(wsrc, (row & (k < K)) ? (uint32_t)((co * N + n) * RS + rs) * 4u : OUTSIDE);
         }
       }
       return;
@@ -552,18 +567,16 @@ __global__ __launch_bounds__(256) void conv_bwd_data_k(ConvBwdDataArgs a) {
   // (one tensor fewer to read), else read
   const float* BG = (bn && a.bn_y && a.bn_gamma) ? a.bn_gamma + (int64_t)j * a.pstride : nullptr;
   const float* BY = (bn && a.bn_y && !BG) ? a.bn_y + (int64_t)j * g.b * N * HW : nullptr;
-  // float4 epilogue when a lane's four pixels never straddle two planes and
-  // every tensor it touches per pixel is 16-byte aligned
+  // grid-only form: float4 access where four consecutive grid points share a
+  // grid row and every tensor touched per pixel is 16-byte aligned
   const uintptr_t align = reinterpret_cast<uintptr_t>(DX) | reinterpret_cast<uintptr_t>(MSK) |
                           reinterpret_cast<uintptr_t>(BX) | reinterpret_cast<uintptr_t>(BY) |
                           (a.add_mode == ADD_SAME ? reinterpret_cast<uintptr_t>(ADD) : 0);
-  const bool vec = (HW & 3) == 0 && (align & 15) == 0;
-  // grid-only form: four consecutive grid points share a grid row
   const bool sp_vec = SP && (g.Wo & 3) == 0 && (align & 15) == 0;
   double s1[TN], s2[TN];
 #pragma unroll
   for (int y = 0; y < TN; ++y) s1[y] = s2[y] = 0.0;
-  if (!SP && vec && a.add_mode != ADD_SUBSAMPLE) {
+  if constexpr (VEC) {
     // The lane's four pixels are consecutive in one plane: float4 access,
     // the operands of a row of TN blocks read before any is used (blocks
     // outside the tensor read element 0 and store nothing).  Reading all
@@ -597,6 +610,33 @@ __global__ __launch_bounds__(256) void conv_bwd_data_k(ConvBwdDataArgs a) {
       };
       if (a.accumulate) read(DX, old);
       if (a.add_mode == ADD_SAME) read(ADD, ad);
+      int sub[4];  // the four pixels' places in the subsampled source, or -1
+      if (ST == 2 && a.add_mode == ADD_SUBSAMPLE) {
+        int ih = it.p / g.W, iw = it.p - ih * g.W;
+        int qh = ih / sst, rh = ih - qh * sst, qw = iw / sst, rw = iw - qw * sst;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          sub[i] = rh == 0 && rw == 0 ? qh * Ws + qw : -1;
+          if (++rw == sst) {
+            rw = 0;
+            ++qw;
+          }
+          if (++iw == g.W) {
+            iw = rw = qw = 0;
+            if (++rh == sst) {
+              rh = 0;
+              ++qh;
+            }
+          }
+        }
+#pragma unroll
+        for (int y = 0; y < TN; ++y) {
+          const int n = n0 + wn0 + y * 16 + (lane & 15);
+          const float* src = ADD + (ok[y] ? ((int64_t)it.img * a.add_C + n) * Hs * Ws : 0);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) ad[y][i] = src[max(sub[i], 0)];
+        }
+      }
       if (MSK) read(MSK, mk);
       if (bn) read(BX, bx);
       if (BY) read(BY, by);
@@ -605,6 +645,10 @@ __global__ __launch_bounds__(256) void conv_bwd_data_k(ConvBwdDataArgs a) {
         v4f v = acc[x][y];
         if (a.accumulate) v += old[y];
         if (a.add_mode == ADD_SAME) v += ad[y];
+        if (ST == 2 && a.add_mode == ADD_SUBSAMPLE)
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (sub[i] >= 0) v[i] += ad[y][i];
         if (MSK)
 #pragma unroll
           for (int i = 0; i < 4; ++i)
@@ -1260,6 +1304,15 @@ hipError_t launch_fwd(const ConvFwdArgs& a, hipStream_t s, const char** name) {
 // Enough workgroups to give every CU at least two.
 constexpr int64_t MIN_WGS = 512;
 
+// Whether the float4 epilogue of a data gradient applies: a lane's four pixels
+// lie in one plane, and every tensor it moves by four pixels is aligned.  A
+// subsampled shortcut starts at a strided layer, so only those kernels add it.
+bool vec_epilogue_ok(const ConvBwdDataArgs& a) {
+  const bool bn = a.bn_part != nullptr, bn_y = bn && a.bn_y && !a.bn_gamma;
+  return (a.g.st == 2 || a.add_mode != ADD_SUBSAMPLE) && a.g.H * a.g.W % 4 == 0 && al16(a.dx) && al16(a.mask) && (!bn || al16(a.bn_x)) &&
+         (!bn_y || al16(a.bn_y)) && (a.add_mode != ADD_SAME || al16(a.add));
+}
+
 template <int BM, int BN, int WM, int WN, int R, int ST, bool SP = false>
 hipError_t launch_bwd_data(const ConvBwdDataArgs& a, hipStream_t s, const char** name) {
   constexpr int BK = stage_k<BM, SP>();
@@ -1269,16 +1322,23 @@ hipError_t launch_bwd_data(const ConvBwdDataArgs& a, hipStream_t s, const char**
   // workgroups per CU slow it down (ResNet-50 k=2 b=32: 274 us per launch
   // with two, 304 with three): unused LDS keeps its 50 KB tiles at two.
   constexpr uint32_t shm = SP && BM == 128 && BN == 64 ? 8192 : 0;
+  auto go = [&](auto ld) {
+    constexpr int LD = decltype(ld)::value;
+    if (!SP && vec_epilogue_ok(a))
+      klaunch((conv_bwd_data_k<BM, BN, WM, WN, R, ST, BK, SP, LD, !SP>), grid, dim3(256), shm, s, a);
+    else
+      klaunch((conv_bwd_data_k<BM, BN, WM, WN, R, ST, BK, SP, LD, false>), grid, dim3(256), shm, s, a);
+    return hipGetLastError();
+  };
   if constexpr (ST == 1 || SP) {
     if (a.g.Co % BK == 0) {
-      klaunch((conv_bwd_data_k<BM, BN, WM, WN, R, ST, BK, SP, TAPS>), grid, dim3(256), shm, s, a);
       if (name) {
         static const std::string n =
             std::string(SP ? tile_name<3, BM, BN, WM, WN, R, ST, BK>() : tile_name<1, BM, BN, WM, WN, R, ST, BK>()) +
             " tap-major";
         *name = n.c_str();
       }
-      return hipGetLastError();
+      return go(std::integral_constant<int, TAPS>());
     }
   }
   // 5x5 layers with less than a workgroup per CU stay on the pointer loads,
@@ -1287,12 +1347,10 @@ hipError_t launch_bwd_data(const ConvBwdDataArgs& a, hipStream_t s, const char**
   // 88 -> 3 channels, 106x106, 2595 and 2457).
   const ConvGeom& g = a.g;
   const bool few = R == 5 && (int64_t)grid.x * grid.y * grid.z < MIN_WGS / 2;
-  if (!few && (int64_t)g.b * g.Co * g.Ho * g.Wo * 4 < OUTSIDE && (int64_t)g.Co * g.Ci * R * R * 4 < OUTSIDE)
-    klaunch((conv_bwd_data_k<BM, BN, WM, WN, R, ST, BK, SP, BUF>), grid, dim3(256), shm, s, a);
-  else
-    klaunch((conv_bwd_data_k<BM, BN, WM, WN, R, ST, BK, SP, PLAIN>), grid, dim3(256), shm, s, a);
   if (name) *name = SP ? tile_name<3, BM, BN, WM, WN, R, ST, BK>() : tile_name<1, BM, BN, WM, WN, R, ST, BK>();
-  return hipGetLastError();
+  if (!few && (int64_t)g.b * g.Co * g.Ho * g.Wo * 4 < OUTSIDE && (int64_t)g.Co * g.Ci * R * R * 4 < OUTSIDE)
+    return go(std::integral_constant<int, BUF>());
+  return go(std::integral_constant<int, PLAIN>());
 }
 
 constexpr int WG_BK = 32;  // pixels per stage of the weight gradient

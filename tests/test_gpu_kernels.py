@@ -600,6 +600,53 @@ def test_conv_data_gradient_epilogue(case):
             assert max_rel(sums[j, :, 1], s2) <= TOL_STEP1, (name, j, "sum d*xh")
 
 
+# The GEMM data gradient's float4 epilogue (planes of a multiple of four
+# pixels): every tile width, quads that straddle rows, the subsampled shortcut;
+# columns as in DGRAD_EPILOGUE
+DGRAD_VEC = [
+    ("vec.3x3s2.acc.mask.sub.bn", 2, 3, 20, 12, 33, 3, 2, 1, 1, 1, 2, 33, 1, 1),
+    ("vec.3x3s2.w6.sub.bn", 1, 2, 7, 6, 19, 3, 2, 1, 0, 0, 2, 19, 1, 0),
+    ("vec.3x3s2.n24.mask.sub.bn", 3, 14, 24, 40, 5, 3, 2, 1, 0, 1, 2, 24, 1, 0),
+    ("vec.3x3s2.n40.acc.sub.bn.relux", 2, 6, 40, 40, 16, 3, 2, 1, 1, 0, 2, 40, 1, 2),
+    ("vec.3x3s2.n40.same.bn", 2, 2, 40, 20, 33, 3, 2, 1, 0, 1, 1, 40, 1, 1),
+    ("vec.3x3.sub.bn", 2, 3, 24, 12, 20, 3, 1, 1, 0, 1, 2, 24, 1, 1),
+    ("vec.1x1s2.pad.same.bn", 1, 2, 20, 8, 12, 1, 2, 1, 1, 1, 1, 20, 1, 1),
+    ("vec.1x1.n512.mask.same.bn.rc", 2, 16, 72, 20, 32, 1, 1, 0, 0, 1, 1, 72, 1, 3),
+]
+
+
+@pytest.mark.parametrize("case", DGRAD_VEC, ids=[c[0] for c in DGRAD_VEC])
+def test_conv_data_gradient_vector_epilogue(case):
+    test_conv_data_gradient_epilogue(case)
+
+
+@pytest.mark.parametrize("R,st,H,Ci,add_mode", [(3, 2, 12, 24, 2), (3, 2, 40, 72, 1), (1, 1, 6, 40, 1)])
+def test_gemm_data_gradient_at_any_float_alignment(R, st, H, Ci, add_mode):
+    """The scalar epilogue, which takes tensors one float past a 16-byte
+    boundary, gives the same bytes as the float4 one."""
+    L, k, b, Co, pad, s = cb.lib(), 2, 5, 20, R // 2, torch.cuda.current_stream().cuda_stream
+    Ho = (H + 2 * pad - R) // st + 1
+    n, nw = k * b * Ci * H * H, Co * Ci * R * R
+    parts = L.cb_test_conv_dgrad_parts(k, b, Ci, H, H, Co, R, st, pad)
+    g = torch.Generator(device="cuda").manual_seed(H)
+    src = torch.randn(5, n, device="cuda", generator=g)
+    w = torch.randn(k * nw, device="cuda", generator=g)
+    dy = torch.randn(k * b * Co * Ho * Ho, device="cuda", generator=g)
+    m = torch.rand(2, k * Ci, device="cuda", generator=g) + 0.5
+    outs = []
+    for off in (0, 1):
+        mask, add, bnx, bny, dx = (torch.empty(n + 4, device="cuda")[off:off + n].copy_(t) for t in src)
+        pt = torch.full((k * Ci * parts * 2,), float("nan"), dtype=torch.float64, device="cuda")
+        assert L.cb_test_conv_dgrad(k, b, Ci, H, H, Co, R, st, pad, dy.data_ptr(), w.data_ptr(), nw,
+                                    dx.data_ptr(), 1, mask.data_ptr(), add.data_ptr(), add_mode, Ci,
+                                    bnx.data_ptr(), bny.data_ptr(), m[0].data_ptr(),
+                                    m[1].data_ptr(), None, pt.data_ptr(), s) == 0
+        torch.cuda.synchronize()
+        outs.append([t.cpu().numpy() for t in (dx, pt)])
+    for a, c in zip(*outs):
+        assert np.isfinite(a).all() and np.array_equal(a, c)
+
+
 # 3x3 stride-1 layers on the direct kernel's flat pixel tiles: per width the
 # fewest channels at these batches that reach each tile (one case below the
 # 14-wide rule stays on the GEMM), with last tiles that are partial and tiles
