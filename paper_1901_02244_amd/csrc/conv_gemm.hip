@@ -61,25 +61,29 @@ __device__ __forceinline__ GemmTile gemm_tile() {
 // and 12-15 of one quad's 16 rows and 4-11 of the next one's, and those of a
 // write that stores four quads per row four rows of each: both fall on
 // distinct banks.  (Rows padded to BK + 4 floats had 0.5 to 0.65 conflict
-// cycles per useful one, and a fifth more LDS.)
-template <int ROWS>
+// cycles per useful one, and a fifth more LDS.)  ONE: quads 4 to 7 also xor the
+// row with 2, for a stage that is stored one float per lane, two rows of
+// eight quads at a time: otherwise quads q and q + 4 of a row share banks.
+template <int ROWS, bool ONE = false>
 __device__ __forceinline__ int quad_at(int row, int quad) {
-  return quad * ROWS + (row ^ (0x84c0 >> (4 * (quad & 3)) & 12));
+  return quad * ROWS + (row ^ (0x84c0 >> (4 * (quad & 3)) & 12) ^ (ONE ? (quad & 4) >> 1 : 0));
 }
 
 // One LDS stage: the products of A rows wm0 + 16 i and B rows wn0 + 16 i.
-template <int BM, int BN, int TM, int TN, int BK>
+template <int BM, int BN, int TM, int TN, int BK, bool ONE = false>
 __device__ __forceinline__ void mma_stage(const v4f* As, const v4f* Bs, int wm0, int wn0,
                                           int lane, v4f (&acc)[TM][TN]) {
-  const v4f* Ar = As + quad_at<BM>(wm0 + (lane & 15), lane >> 4);
-  const v4f* Br = Bs + quad_at<BN>(wn0 + (lane & 15), lane >> 4);
+  const int ra = wm0 + (lane & 15), rb = wn0 + (lane & 15), q = lane >> 4;
+  const int a0 = quad_at<BM>(ra, q), b0 = quad_at<BN>(rb, q);
 #pragma unroll
   for (int g = 0; g < BK; g += 16) {
+    const v4f* Ar = As + (ONE && g ? quad_at<BM, true>(ra, q + 4) : a0 + g / 4 * BM);
+    const v4f* Br = Bs + (ONE && g ? quad_at<BN, true>(rb, q + 4) : b0 + g / 4 * BN);
     v4f av[TM], bv[TN];
 #pragma unroll
-    for (int i = 0; i < TM; ++i) av[i] = Ar[g / 4 * BM + i * 16];
+    for (int i = 0; i < TM; ++i) av[i] = Ar[i * 16];
 #pragma unroll
-    for (int i = 0; i < TN; ++i) bv[i] = Br[g / 4 * BN + i * 16];
+    for (int i = 0; i < TN; ++i) bv[i] = Br[i * 16];
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk)
 #pragma unroll
@@ -859,9 +863,13 @@ __global__ __launch_bounds__(256, VEC && BM == 128 ? (BN == 64 ? 4 : 5) : 1) voi
 // a thread loads one pixel of four times as many rows.  The kernel is limited
 // by its loads: ResNet-50's flat layers (k=2 b=32) took 92 us per launch with
 // one pixel per load and take 73 with quads; its 7 x 7 layers measured slower
-// with four single loads per row (1x1 93 -> 135, 3x3 236 -> 289 us).
+// with four single loads per row (1x1 93 -> 135, 3x3 236 -> 289 us).  One pixel
+// at a time, with a quad's row xor (quad_at's ONE) and the LDS places from a
+// few bases, and 16-row tiles held to seven waves per SIMD by the launch
+// bounds: 48 -> 16 channels 5x5, 62x62, k=5 b=32 555 -> 530 us, 16 -> 16 3x3, 40x40,
+// k=4 b=32 37.2 -> 36.0.
 template <int BM, int BN, int WM, int WN, int R, int BK, bool QUADS, bool FLAT>
-__global__ __launch_bounds__(256) void conv_bwd_weight_k(ConvBwdWeightArgs a) {
+__global__ __launch_bounds__(256, BM == 16 && !QUADS ? 7 : 1) void conv_bwd_weight_k(ConvBwdWeightArgs a) {
   static_assert(!FLAT || (QUADS && R == 1), "flat X pixels are quads of a 1x1 layer");
   constexpr int RS = R * R;
   constexpr int TM = BM / (WM * 16), TN = BN / (WN * 16);
@@ -961,15 +969,25 @@ __global__ __launch_bounds__(256) void conv_bwd_weight_k(ConvBwdWeightArgs a) {
       }
     }
   };
+  // LDS places of this thread's rows rg, rg + RG, ...: the swizzle repeats
+  // every 16 rows, so NB bases and constant steps of 16 rows reach them all
+  constexpr bool ONE = !QUADS && BK == 32;
+  constexpr int NB = RG < 16 ? 16 / RG : 1;
+  int pa[NB], pb[NB];
+#pragma unroll
+  for (int i = 0; i < NB; ++i) {
+    pa[i] = quad_at<BM, ONE>(rg + RG * i, PX * q4 / 4);
+    pb[i] = quad_at<BN, ONE>(rg + RG * i, PX * q4 / 4);
+  }
   auto put = [&](v4f* quad, vpx v) {
     reinterpret_cast<vpx*>(quad)[QUADS ? 0 : q4 & 3] = v;
   };
   auto store = [&](int buf) {
 #pragma unroll
     for (int i = 0; i < RA; ++i)
-      if (BM % RG == 0 || rg + RG * i < BM) put(&As[buf][quad_at<BM>(rg + RG * i, PX * q4 / 4)], ra[i]);
+      if (BM % RG == 0 || rg + RG * i < BM) put(&As[buf][pa[i % NB] + RG * (i / NB * NB)], ra[i]);
 #pragma unroll
-    for (int i = 0; i < RB; ++i) put(&Bs[buf][quad_at<BN>(rg + RG * i, PX * q4 / 4)], rb[i]);
+    for (int i = 0; i < RB; ++i) put(&Bs[buf][pb[i % NB] + RG * (i / NB * NB)], rb[i]);
   };
 
   v4f acc[TM][TN];
@@ -988,7 +1006,7 @@ __global__ __launch_bounds__(256) void conv_bwd_weight_k(ConvBwdWeightArgs a) {
       advance();
       load();
     }
-    mma_stage<BM, BN, TM, TN, BK>(As[cur], Bs[cur], wm0, wn0, lane, acc);
+    mma_stage<BM, BN, TM, TN, BK, ONE>(As[cur], Bs[cur], wm0, wn0, lane, acc);
     if (t + 1 < T) store(cur ^ 1);
     __syncthreads();
   }
