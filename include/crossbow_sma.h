@@ -245,6 +245,25 @@ int cb_test_conv(int k, int b, int Ci, int H, int W, int Co, int R, int stride, 
                  float* y, double* stats, const float* dy, float* dx, float* grads,
                  void* scratch, size_t scratch_bytes, void* stream);
 
+/* 1 if the implicit GEMM reads this layer's forward (or, with
+ * data_gradient, data-gradient) operands by pointer, because a replica's
+ * input tensor or the filter reaches the 2 GiB that its buffer loads allow;
+ * 0 if by buffer; CB_EINVAL on a bad shape.  Pure host function. */
+int cb_test_conv_by_pointer(int k, int b, int Ci, int H, int W, int Co, int R, int stride, int pad,
+                            int data_gradient);
+
+/* cb_test_conv with those pointer loads at any size, for the layers whose
+ * forward and data gradient run on the implicit GEMM. */
+int cb_test_conv_pointers(int k, int b, int Ci, int H, int W, int Co, int R, int stride, int pad,
+                          int relu, int has_bias, const float* x, const float* params,
+                          int64_t pstride, float* y, double* stats, const float* dy, float* dx,
+                          float* grads, void* scratch, size_t scratch_bytes, void* stream);
+
+/* Name of the kernel that the calling thread's last convolution hook
+ * launched: which = 0 the forward, 1 the weight gradient, 2 the data
+ * gradient ("" if it launched none). */
+const char* cb_test_conv_kernel(int which);
+
 /* Scratch for the batch-norm hooks; 0 on bad shape. */
 size_t cb_test_bn_scratch_bytes(int k, int b, int C, int H, int W);
 
@@ -298,6 +317,14 @@ int cb_test_conv_dgrad(int k, int b, int Ci, int H, int W, int Co, int R, int st
                        int add_C, const float* bn_x, const float* bn_y, const float* bn_mean,
                        const float* bn_istd, const float* bn_gamma, double* bn_part,
                        void* stream);
+
+/* The same with the implicit GEMM's pointer loads (cb_test_conv_pointers). */
+int cb_test_conv_dgrad_pointers(int k, int b, int Ci, int H, int W, int Co, int R, int stride,
+                                int pad, const float* dy, const float* params, int64_t pstride,
+                                float* dx, int accumulate, const float* mask, const float* add,
+                                int add_mode, int add_C, const float* bn_x, const float* bn_y,
+                                const float* bn_mean, const float* bn_istd, const float* bn_gamma,
+                                double* bn_part, void* stream);
 
 /* 1 if the fused network head takes C channels of H x W pixels and
  * `classes` outputs, else 0. */

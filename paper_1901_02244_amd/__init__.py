@@ -39,7 +39,8 @@ EXPORTS = (
     "cb_test_conv_scratch_bytes", "cb_test_conv", "cb_test_bn_scratch_bytes", "cb_test_bn_fwd",
     "cb_test_bn_bwd", "cb_test_maxpool", "cb_test_softmax_xent",
     "cb_set_lr", "cb_restart", "cb_set_learners", "cb_learners", "cb_tuner_next",
-    "cb_test_conv_dgrad_parts", "cb_test_conv_dgrad", "cb_set_graphs",
+    "cb_test_conv_dgrad_parts", "cb_test_conv_dgrad", "cb_set_graphs", "cb_test_conv_by_pointer",
+    "cb_test_conv_pointers", "cb_test_conv_dgrad_pointers", "cb_test_conv_kernel",
 )
 
 
@@ -117,6 +118,10 @@ def lib():
         L.cb_test_conv_fwd_parts.argtypes = [_i] * 9
         L.cb_test_conv.argtypes = [_i] * 11 + [_P, _P, ctypes.c_int64, _P, _P, _P, _P, _P, _P,
                                                ctypes.c_size_t, _P]
+        L.cb_test_conv_pointers.argtypes = L.cb_test_conv.argtypes
+        L.cb_test_conv_by_pointer.argtypes = [_i] * 10
+        L.cb_test_conv_kernel.argtypes = [_i]
+        L.cb_test_conv_kernel.restype = ctypes.c_char_p
         L.cb_test_conv_static.argtypes = [_i] * 11 + [_P, _P, ctypes.c_int64, _P, _P, _P, _P,
                                                       _P, _P]
         L.cb_test_head_ok.argtypes = [_i] * 4
@@ -133,6 +138,7 @@ def lib():
         L.cb_test_conv_dgrad_parts.argtypes = [_i] * 9
         L.cb_test_conv_dgrad.argtypes = [_i] * 9 + [_P, _P, ctypes.c_int64, _P, _i, _P, _P, _i, _i,
                                                     _P, _P, _P, _P, _P, _P, _P]
+        L.cb_test_conv_dgrad_pointers.argtypes = L.cb_test_conv_dgrad.argtypes
         L.cb_set_lr.argtypes = [_P, ctypes.c_float]
         L.cb_restart.argtypes = [_P]
         L.cb_set_learners.argtypes = [_P, _i, ctypes.c_float]

@@ -1449,13 +1449,18 @@ bool direct_large(int k, int b, int W, int Cout, bool flip) {
          (int64_t)k * cdiv((int64_t)b * W * W, 128) * cdiv(Cout, 64) >= DIRECT_MIN_WGS / 4;
 }
 
+// The buffers of one tile (the filter, the up to `images` images it touches)
+// have 32-bit offsets below OUTSIDE.
+bool direct_bytes_ok(const ConvGeom& g, bool flip, int images) {
+  const int64_t image = flip ? (int64_t)g.Co * g.Ho * g.Wo : (int64_t)g.Ci * g.H * g.W;
+  return (int64_t)g.Ci * g.Co * 36 < OUTSIDE && image * 4 * images < OUTSIDE;
+}
+
 bool direct_ok(const ConvGeom& g, bool flip) {
   if (g.R != 3 || g.S != 3 || g.st != 1 || g.pad != 1 || g.H != g.W) return false;
   const int Cin = flip ? g.Co : g.Ci, Cout = flip ? g.Ci : g.Co;
   if (Cin % 16 || Cout % 16) return false;
-  // the buffers of one tile (the filter, the up to four images a flat tile
-  // touches) have 32-bit offsets below OUTSIDE
-  if ((int64_t)Cin * Cout * 36 >= OUTSIDE || (int64_t)Cin * g.H * g.W * 16 >= OUTSIDE) return false;
+  if (!direct_bytes_ok(g, flip, 4)) return false;
   return direct_small(g.W) || direct_large(g.k, g.b, g.W, Cout, flip);
 }
 
@@ -1583,7 +1588,8 @@ int s2_tho(int WO) { return WO == 16 ? 4 : 8; }
 
 bool conv_s2_dgrad_ok(const ConvGeom& g) {
   return g.R == 3 && g.S == 3 && g.st == 2 && g.pad == 1 && g.H == g.W && g.H % 2 == 0 &&
-         (g.W == 16 || g.W == 32) && g.Ho == g.H / 2 && g.Ci % 16 == 0 && g.Co % 16 == 0;
+         (g.W == 16 || g.W == 32) && g.Ho == g.H / 2 && g.Ci % 16 == 0 && g.Co % 16 == 0 &&
+         direct_bytes_ok(g, true, 1);
 }
 
 int conv_s2_dgrad_tiles(const ConvGeom& g) { return g.b * (g.Ho / s2_tho(g.Wo)); }
@@ -1607,7 +1613,7 @@ hipError_t conv_s2_dgrad(const ConvBwdDataArgs& d, hipStream_t s, const char** n
 bool direct_s2_ok(const ConvGeom& g) {
   return g.R == 3 && g.S == 3 && g.st == 2 && g.pad == 1 && g.H == g.W && g.H % 2 == 0 &&
          (g.W == 16 || g.W == 32) && g.Ho == g.H / 2 && g.Wo == g.W / 2 && g.Ci % 16 == 0 &&
-         g.Co % 16 == 0;
+         g.Co % 16 == 0 && direct_bytes_ok(g, false, 1);
 }
 
 bool conv_direct_wgrad_ok(const ConvGeom& g) {
@@ -1646,7 +1652,7 @@ hipError_t conv_direct_wgrad(const ConvBwdWeightArgs& w, hipStream_t s, const ch
 bool conv_flat_wgrad_ok(const ConvGeom& g, int chunk) {
   if (g.R != 3 || g.S != 3 || g.st != 1 || g.pad != 1 || g.H != g.W) return false;
   if ((g.W != 14 && g.W != 28 && g.W != 56) || g.Ci % 32 || g.Co % 32) return false;
-  if ((int64_t)g.Ci * g.H * g.W * 16 >= OUTSIDE) return false;  // 32-bit offsets, as direct_ok
+  if (!direct_bytes_ok(g, false, 4)) return false;
   return chunk >= (g.W == 14 ? 224 : 384);
 }
 

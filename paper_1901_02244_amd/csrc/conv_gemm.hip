@@ -112,15 +112,22 @@ __device__ __forceinline__ float relu0(float v) { return v > 0.f ? v : 0.f; }
 __device__ __forceinline__ double shfl_xor_d(double v, int o) { return __shfl_xor(v, o, 64); }
 
 // ---------------------------------------------------------------- forward
-// CF (Ci a multiple of BK): the contraction runs over k = (channel block of
-// BK, r, s, channel in the block) instead of (ci, r, s), the same sum in
+// The loads of the forward and the data gradient.  PLAIN: by pointer, for
+// tensors past the 32-bit offsets of a buffer (conv_by_pointer); TAPS and BUF:
+// buffer loads without branches, every window check a bit of a mask.
+enum ConvLoad { PLAIN, TAPS, BUF };
+
+// LD BUF, PLAIN: the contraction runs over k = (ci, r, s).  LD TAPS (Ci a
+// multiple of BK): over k = (channel block of
+// BK, r, s, channel in the block), the same sum in
 // another order (the same order for 1x1 filters).  A stage of BK steps then
 // shares one tap (r, s), so its window check and tap offset are computed
 // once per stage, and a thread's steps are consecutive channels (one plane
 // apart in X, RS floats apart in W); the R*R taps of a channel block follow
 // each other, so its planes stay in L2 across them.
-template <int BM, int BN, int WM, int WN, int R, int BK, bool CF = false>
+template <int BM, int BN, int WM, int WN, int R, int BK, int LD>
 __global__ __launch_bounds__(256) void conv_fwd_k(ConvFwdArgs a) {
+  constexpr bool CF = LD == TAPS;
   constexpr int RS = R * R;
   constexpr int TM = BM / (WM * 16), TN = BN / (WN * 16);
   constexpr int TPR = 256 / BM;   // threads sharing one output row
@@ -145,17 +152,18 @@ __global__ __launch_bounds__(256) void conv_fwd_k(ConvFwdArgs a) {
   const int akq = __builtin_amdgcn_readfirstlane(tid / BM);
   // The lane's output pixel: element offset of its window corner (ih0, iw0)
   // and, as bit masks, the window rows and columns that lie inside the
-  // image (none past the last pixel).  Every load below is a buffer load
-  // whose offset is OUTSIDE where the element is zero, so the loaders have
-  // no branches.
+  // image (none past the last pixel).  Every buffer load below has the offset
+  // OUTSIDE where the element is zero, so its loader has no branches.
   int xb = 0;
+  const float* xp = X;  // PLAIN: the corner itself
   uint32_t rmask = 0, cmask = 0;
   {
     const int m = m0 + am;
     if (m < M) {
       const int img = m / HoWo, p = m - img * HoWo, oh = p / g.Wo, ow = p - oh * g.Wo;
       const int ih0 = oh * g.st - g.pad, iw0 = ow * g.st - g.pad;
-      xb = img * g.Ci * HW + ih0 * g.W + iw0;
+      if (LD == PLAIN) xp += (int64_t)img * g.Ci * HW + ih0 * g.W + iw0;
+      else xb = img * g.Ci * HW + ih0 * g.W + iw0;
 #pragma unroll
       for (int r = 0; r < R; ++r) {
         if ((unsigned)(ih0 + r) < (unsigned)g.H) rmask |= 1u << r;
@@ -171,6 +179,16 @@ __global__ __launch_bounds__(256) void conv_fwd_k(ConvFwdArgs a) {
   float rb[BPT][4];
 
   auto loadA = [&](int k0, float (&ra)[KPT]) {
+    if constexpr (LD == PLAIN) {
+#pragma unroll
+      for (int i = 0; i < KPT; ++i) {
+        const int k = k0 + akq * KPT + i;
+        const int ci = k / RS, rs = k - ci * RS, r = rs / R, s = rs - r * R;
+        ra[i] = 0.f;
+        if (k < K && ((rmask >> r) & (cmask >> s) & 1u)) ra[i] = xp[ci * HW + r * g.W + s];
+      }
+      return;
+    }
     const auto xsrc = buf_rsrc_u(X, xbytes);
     if constexpr (CF) {
       const int t = k0 / BK, blk = t / RS, rs = t - blk * RS, r = rs / R, s = rs - r * R;
@@ -192,6 +210,18 @@ __global__ __launch_bounds__(256) void conv_fwd_k(ConvFwdArgs a) {
     }
   };
   auto loadB = [&](int k0, float (&rb)[BPT][4]) {
+    if constexpr (LD == PLAIN) {
+#pragma unroll
+      for (int u = 0; u < BPT; ++u) {
+        const int idx = tid + u * 256, n = n0 + idx / QPR, kq = k0 + 4 * (idx % QPR);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          rb[u][i] = 0.f;
+          if (idx < BQ && n < N && kq + i < K) rb[u][i] = Wt[(int64_t)n * K + kq + i];
+        }
+      }
+      return;
+    }
     const auto wsrc = buf_rsrc_u(Wt, wbytes);
     if constexpr (CF) {
       const int t = k0 / BK, blk = t / RS, rs = t - blk * RS, c0 = blk * BK;
@@ -367,8 +397,6 @@ __global__ __launch_bounds__(256) void conv_fwd_k(ConvFwdArgs a) {
 // 20x20, 512 -> 128 1x1, k=2 b=16 53 -> 48 us; ResNet-50 k=2 b=32 23.05 -> 22.87 ms a
 // step.  A subsampled shortcut is added here too (98x98, 128 -> 16 3x3 stride 2,
 // k=3 b=48: 1337 us, through the scalar epilogue 3204).
-enum GradLoad { PLAIN, TAPS, BUF };
-
 template <int BM, int BN, int WM, int WN, int R, int ST, int BK, bool SP, int LD, bool VEC>
 __global__ __launch_bounds__(256, VEC && BM == 128 ? (BN == 64 ? 4 : 5) : 1) void conv_bwd_data_k(ConvBwdDataArgs a) {
   constexpr bool CF = LD == TAPS;
@@ -397,19 +425,20 @@ __global__ __launch_bounds__(256, VEC && BM == 128 ? (BN == 64 ? 4 : 5) : 1) voi
 
   const int am = tid % BM;
   const int akq = __builtin_amdgcn_readfirstlane(tid / BM);
-  int thp = OUT_OF_RANGE, twp = OUT_OF_RANGE, yb = 0;
+  int thp = OUT_OF_RANGE, twp = OUT_OF_RANGE;
+  std::conditional_t<LD == PLAIN, int64_t, int> yb = 0;
   {
     const int m = m0 + am;
     if (m < M) {
       if (SP) {  // m is a grid point: dY pixel m % HoWo of image m / HoWo
         const int img = m / HoWo;
         thp = twp = 0;
-        yb = img * g.Co * HoWo + (m - img * HoWo);
+        yb = (decltype(yb))img * g.Co * HoWo + (m - img * HoWo);
       } else {
         const int img = m / HW, p = m - img * HW, ih = p / g.W, iw = p - ih * g.W;
         thp = ih + g.pad;
         twp = iw + g.pad;
-        yb = img * g.Co * HoWo;
+        yb = (decltype(yb))img * g.Co * HoWo;
       }
     }
   }
@@ -1290,6 +1319,15 @@ const char* tile_name() {
   return n.c_str();
 }
 
+// The same with the loads (and the float4 epilogue) of a forward or data gradient.
+template <int KIND, int BM, int BN, int WM, int WN, int R, int ST, int BK, int LD, bool VEC = false>
+const char* load_name() {
+  static const std::string n = std::string(tile_name<KIND, BM, BN, WM, WN, R, ST, BK>()) +
+                               (LD == PLAIN ? " by pointer" : LD == TAPS ? " tap-major" : "") +
+                               (VEC ? " float4" : "");
+  return n.c_str();
+}
+
 // LDS stage depth: 32 contraction steps, 16 for tiles of 128 rows or more
 // (the 1x1 stride-2 grid-only data gradient from 256 rows: its 128-row
 // tiles measured slower with 16).  The shallow stage halves the LDS of a
@@ -1306,17 +1344,15 @@ hipError_t launch_fwd(const ConvFwdArgs& a, hipStream_t s, const char** name) {
   constexpr int BK = stage_k<BM>();
   const int M = a.g.b * a.g.Ho * a.g.Wo;
   dim3 grid(cdiv(M, BM), cdiv(a.g.Co, BN), a.g.k);
-  if (a.g.Ci % BK == 0) {
-    klaunch((conv_fwd_k<BM, BN, WM, WN, R, BK, true>), grid, dim3(256), 0, s, a);
-    if (name) {
-      static const std::string n = std::string(tile_name<0, BM, BN, WM, WN, R, 0, BK>()) + " tap-major";
-      *name = n.c_str();
-    }
+  auto go = [&](auto ld) {
+    constexpr int LD = decltype(ld)::value;
+    klaunch((conv_fwd_k<BM, BN, WM, WN, R, BK, LD>), grid, dim3(256), 0, s, a);
+    if (name) *name = load_name<0, BM, BN, WM, WN, R, 0, BK, LD>();
     return hipGetLastError();
-  }
-  klaunch((conv_fwd_k<BM, BN, WM, WN, R, BK>), grid, dim3(256), 0, s, a);
-  if (name) *name = tile_name<0, BM, BN, WM, WN, R, 0, BK>();
-  return hipGetLastError();
+  };
+  if (a.by_pointer || conv_by_pointer(a.g, false)) return go(std::integral_constant<int, PLAIN>());
+  if (a.g.Ci % BK == 0) return go(std::integral_constant<int, TAPS>());
+  return go(std::integral_constant<int, BUF>());
 }
 
 // Enough workgroups to give every CU at least two.
@@ -1342,32 +1378,26 @@ hipError_t launch_bwd_data(const ConvBwdDataArgs& a, hipStream_t s, const char**
   constexpr uint32_t shm = SP && BM == 128 && BN == 64 ? 8192 : 0;
   auto go = [&](auto ld) {
     constexpr int LD = decltype(ld)::value;
-    if (!SP && vec_epilogue_ok(a))
-      klaunch((conv_bwd_data_k<BM, BN, WM, WN, R, ST, BK, SP, LD, !SP>), grid, dim3(256), shm, s, a);
-    else
+    constexpr bool VEC = !SP && (LD != PLAIN || R == 5);
+    constexpr int KIND = SP ? 3 : 1;
+    if (VEC && vec_epilogue_ok(a)) {
+      klaunch((conv_bwd_data_k<BM, BN, WM, WN, R, ST, BK, SP, LD, VEC>), grid, dim3(256), shm, s, a);
+      if (name) *name = load_name<KIND, BM, BN, WM, WN, R, ST, BK, LD, VEC>();
+    } else {
       klaunch((conv_bwd_data_k<BM, BN, WM, WN, R, ST, BK, SP, LD, false>), grid, dim3(256), shm, s, a);
+      if (name) *name = load_name<KIND, BM, BN, WM, WN, R, ST, BK, LD>();
+    }
     return hipGetLastError();
   };
-  if constexpr (ST == 1 || SP) {
-    if (a.g.Co % BK == 0) {
-      if (name) {
-        static const std::string n =
-            std::string(SP ? tile_name<3, BM, BN, WM, WN, R, ST, BK>() : tile_name<1, BM, BN, WM, WN, R, ST, BK>()) +
-            " tap-major";
-        *name = n.c_str();
-      }
-      return go(std::integral_constant<int, TAPS>());
-    }
-  }
+  if (a.by_pointer || conv_by_pointer(a.g, true)) return go(std::integral_constant<int, PLAIN>());
+  if constexpr (ST == 1 || SP)
+    if (a.g.Co % BK == 0) return go(std::integral_constant<int, TAPS>());
   // 5x5 layers with less than a workgroup per CU stay on the pointer loads,
   // which skip what the window leaves out (882 -> 12 channels, 13x13, 14
   // workgroups: the whole layer 951 us, by buffer 1032; with 2800 workgroups,
   // 88 -> 3 channels, 106x106, 2595 and 2457).
-  const ConvGeom& g = a.g;
   const bool few = R == 5 && (int64_t)grid.x * grid.y * grid.z < MIN_WGS / 2;
-  if (name) *name = SP ? tile_name<3, BM, BN, WM, WN, R, ST, BK>() : tile_name<1, BM, BN, WM, WN, R, ST, BK>();
-  if (!few && (int64_t)g.b * g.Co * g.Ho * g.Wo * 4 < OUTSIDE && (int64_t)g.Co * g.Ci * R * R * 4 < OUTSIDE)
-    return go(std::integral_constant<int, BUF>());
+  if (!few) return go(std::integral_constant<int, BUF>());
   return go(std::integral_constant<int, PLAIN>());
 }
 
@@ -1479,6 +1509,11 @@ hipError_t bwd_weight_r(const ConvBwdWeightArgs& a, hipStream_t s, const char** 
 }  // namespace
 
 inline bool al8(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 7) == 0; }
+
+bool conv_by_pointer(const ConvGeom& g, bool bwd_data) {
+  const int64_t in = bwd_data ? (int64_t)g.Co * g.Ho * g.Wo : (int64_t)g.Ci * g.H * g.W;
+  return g.b * in * 4 >= OUTSIDE || (int64_t)g.Co * g.Ci * g.R * g.S * 4 >= OUTSIDE;
+}
 
 int conv_fwd_tiles_m(const ConvGeom& g) {
   if (conv_direct_fwd_ok(g)) return conv_direct_fwd_tiles(g);
@@ -1613,6 +1648,10 @@ hipError_t conv_bwd_weight(const ConvBwdWeightArgs& a, hipStream_t s, const char
   if (conv_direct_wgrad_ok(a.g))  // reads dY in 16-byte pieces
     return al16(a.dy) ? conv_direct_wgrad(a, s, name) : hipErrorInvalidValue;
   if (conv_flat_wgrad_ok(a.g, a.chunk)) return conv_flat_wgrad(a, s, name);
+  // 32-bit element offsets from the replica's tensors
+  const int64_t images = a.g.b, limit = (int64_t)1 << 31;
+  if (images * a.g.Ci * a.g.H * a.g.W >= limit || images * a.g.Co * a.g.Ho * a.g.Wo >= limit)
+    return hipErrorInvalidValue;
   switch (a.g.R) {
     case 1: return bwd_weight_r<1>(a, s, name);
     case 3: return bwd_weight_r<3>(a, s, name);

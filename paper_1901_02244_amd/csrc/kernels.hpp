@@ -104,6 +104,7 @@ struct ConvFwdArgs {
   // stored outputs of each M tile, [k][Co][tiles_m][2], for the batch norm
   // that consumes y (tiles_m = conv_fwd_tiles_m).
   double* stats;
+  bool by_pointer = false;  // the implicit GEMM's pointer loads at any size (tests)
 };
 
 // Residual added to a data gradient (the shortcut of a residual block):
@@ -149,6 +150,7 @@ struct ConvBwdDataArgs {
   // the direct kernels then take the mask's decision as bn_affine of bn_x
   // instead of reading the mask.
   bool mask_from_bn = false;
+  bool by_pointer = false;  // the implicit GEMM's pointer loads at any size (tests)
 };
 
 struct ConvBwdWeightArgs {
@@ -170,6 +172,11 @@ int conv_fwd_tiles_m(const ConvGeom& g);
 int conv_bwd_data_tiles_m(const ConvGeom& g);
 // Split of the weight-gradient contraction; exposed so the host can size scratch.
 int conv_bwd_weight_splits(const ConvGeom& g, int* chunk);
+
+// Whether the implicit GEMM's forward or data gradient reads X or dY and the
+// filter by pointer: where a replica's tensor reaches OUTSIDE (2 GiB), past
+// which the offset that marks a zero element of a buffer would lie inside it.
+bool conv_by_pointer(const ConvGeom& g, bool bwd_data);
 
 // The conv launchers pick a tile shape from the layer's sizes; *name (if
 // not null) receives the launched kernel's name, for instrumentation.

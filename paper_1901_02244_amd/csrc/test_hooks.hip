@@ -32,6 +32,10 @@ bool geom_ok(int k, int b, int Ci, int H, int W, int Co, int R, int st, int pad)
 
 int rc_of(hipError_t e) { return e == hipSuccess ? CB_OK : CB_EDEVICE; }
 
+// Kernels this thread's last convolution hook launched: forward, weight
+// gradient, data gradient.
+thread_local const char* conv_kernel[3] = {"", "", ""};
+
 }  // namespace
 
 extern "C" {
@@ -52,10 +56,10 @@ int cb_test_conv_fwd_parts(int k, int b, int Ci, int H, int W, int Co, int R, in
   return conv_fwd_tiles_m(make_geom(k, b, Ci, H, W, Co, R, stride, pad));
 }
 
-int cb_test_conv(int k, int b, int Ci, int H, int W, int Co, int R, int stride, int pad,
-                 int relu, int has_bias, const float* x, const float* params, int64_t pstride,
-                 float* y, double* stats, const float* dy, float* dx, float* grads,
-                 void* scratch, size_t scratch_bytes, void* stream) {
+static int run_conv(int k, int b, int Ci, int H, int W, int Co, int R, int stride, int pad,
+                    int relu, int has_bias, const float* x, const float* params, int64_t pstride,
+                    float* y, double* stats, const float* dy, float* dx, float* grads,
+                    void* scratch, size_t scratch_bytes, void* stream, bool by_pointer) {
   if (!geom_ok(k, b, Ci, H, W, Co, R, stride, pad) ||
       !conv_supported(R, R, stride, dx != nullptr) || !x || !params || !y)
     return CB_EINVAL;
@@ -73,7 +77,9 @@ int cb_test_conv(int k, int b, int Ci, int H, int W, int Co, int R, int stride, 
   f.y = y;
   f.relu = relu;
   f.stats = stats;
-  int rc = rc_of(conv_fwd(f, s));
+  f.by_pointer = by_pointer;
+  conv_kernel[0] = conv_kernel[1] = conv_kernel[2] = "";
+  int rc = rc_of(conv_fwd(f, s, &conv_kernel[0]));
   if (rc || !dy) return rc;
   if (!grads) return CB_EINVAL;
   if (has_bias) {
@@ -88,7 +94,7 @@ int cb_test_conv(int k, int b, int Ci, int H, int W, int Co, int R, int stride, 
   w.pstride = pstride;
   w.partial = static_cast<float*>(scratch);
   w.splits = conv_bwd_weight_splits(g, &w.chunk);
-  rc = rc_of(conv_bwd_weight(w, s));
+  rc = rc_of(conv_bwd_weight(w, s, &conv_kernel[1]));
   if (rc) return rc;
   if (w.splits > 1) {
     SplitTable t;
@@ -111,8 +117,37 @@ int cb_test_conv(int k, int b, int Ci, int H, int W, int Co, int R, int stride, 
   d.add_st = 1;
   d.bn_part = nullptr;
   d.bn_x = d.bn_y = d.bn_mean = d.bn_istd = nullptr;
-  return rc_of(conv_bwd_data(d, s));
+  d.by_pointer = by_pointer;
+  return rc_of(conv_bwd_data(d, s, &conv_kernel[2]));
 }
+
+int cb_test_conv(int k, int b, int Ci, int H, int W, int Co, int R, int stride, int pad,
+                 int relu, int has_bias, const float* x, const float* params, int64_t pstride,
+                 float* y, double* stats, const float* dy, float* dx, float* grads,
+                 void* scratch, size_t scratch_bytes, void* stream) {
+  return run_conv(k, b, Ci, H, W, Co, R, stride, pad, relu, has_bias, x, params, pstride, y, stats,
+                  dy, dx, grads, scratch, scratch_bytes, stream, false);
+}
+
+int cb_test_conv_pointers(int k, int b, int Ci, int H, int W, int Co, int R, int stride, int pad,
+                          int relu, int has_bias, const float* x, const float* params,
+                          int64_t pstride, float* y, double* stats, const float* dy, float* dx,
+                          float* grads, void* scratch, size_t scratch_bytes, void* stream) {
+  return run_conv(k, b, Ci, H, W, Co, R, stride, pad, relu, has_bias, x, params, pstride, y, stats,
+                  dy, dx, grads, scratch, scratch_bytes, stream, true);
+}
+
+int cb_test_conv_by_pointer(int k, int b, int Ci, int H, int W, int Co, int R, int stride, int pad,
+                            int data_gradient) {
+  if (!geom_ok(k, b, Ci, H, W, Co, R, stride, pad) || !conv_supported(R, R, stride, data_gradient))
+    return CB_EINVAL;
+  return conv_by_pointer(make_geom(k, b, Ci, H, W, Co, R, stride, pad), data_gradient) ? 1 : 0;
+}
+
+const char* cb_test_conv_kernel(int which) {
+  return which >= 0 && which < 3 ? conv_kernel[which] : "";
+}
+
 
 int cb_test_conv_dgrad_parts(int k, int b, int Ci, int H, int W, int Co, int R, int stride,
                              int pad) {
@@ -121,12 +156,12 @@ int cb_test_conv_dgrad_parts(int k, int b, int Ci, int H, int W, int Co, int R, 
   return conv_bwd_data_tiles_m(make_geom(k, b, Ci, H, W, Co, R, stride, pad));
 }
 
-int cb_test_conv_dgrad(int k, int b, int Ci, int H, int W, int Co, int R, int stride, int pad,
-                       const float* dy, const float* params, int64_t pstride, float* dx,
-                       int accumulate, const float* mask, const float* add, int add_mode,
-                       int add_C, const float* bn_x, const float* bn_y, const float* bn_mean,
-                       const float* bn_istd, const float* bn_gamma, double* bn_part,
-                       void* stream) {
+static int run_conv_dgrad(int k, int b, int Ci, int H, int W, int Co, int R, int stride, int pad,
+                          const float* dy, const float* params, int64_t pstride, float* dx,
+                          int accumulate, const float* mask, const float* add, int add_mode,
+                          int add_C, const float* bn_x, const float* bn_y, const float* bn_mean,
+                          const float* bn_istd, const float* bn_gamma, double* bn_part,
+                          void* stream, bool by_pointer) {
   if (!geom_ok(k, b, Ci, H, W, Co, R, stride, pad) || !conv_supported(R, R, stride, true) ||
       !dy || !params || !dx || add_mode < ADD_NONE || add_mode > ADD_SUBSAMPLE ||
       (add_mode != ADD_NONE && !add) || (bn_part && (!bn_x || !bn_mean || !bn_istd)) ||
@@ -151,7 +186,31 @@ int cb_test_conv_dgrad(int k, int b, int Ci, int H, int W, int Co, int R, int st
   d.bn_istd = bn_istd;
   d.bn_gamma = bn_gamma;
   d.mask_from_bn = bn_gamma && !bn_y;
-  return rc_of(conv_bwd_data(d, static_cast<hipStream_t>(stream)));
+  d.by_pointer = by_pointer;
+  conv_kernel[0] = conv_kernel[1] = conv_kernel[2] = "";
+  return rc_of(conv_bwd_data(d, static_cast<hipStream_t>(stream), &conv_kernel[2]));
+}
+
+int cb_test_conv_dgrad(int k, int b, int Ci, int H, int W, int Co, int R, int stride, int pad,
+                       const float* dy, const float* params, int64_t pstride, float* dx,
+                       int accumulate, const float* mask, const float* add, int add_mode,
+                       int add_C, const float* bn_x, const float* bn_y, const float* bn_mean,
+                       const float* bn_istd, const float* bn_gamma, double* bn_part,
+                       void* stream) {
+  return run_conv_dgrad(k, b, Ci, H, W, Co, R, stride, pad, dy, params, pstride, dx, accumulate,
+                        mask, add, add_mode, add_C, bn_x, bn_y, bn_mean, bn_istd, bn_gamma,
+                        bn_part, stream, false);
+}
+
+int cb_test_conv_dgrad_pointers(int k, int b, int Ci, int H, int W, int Co, int R, int stride,
+                                int pad, const float* dy, const float* params, int64_t pstride,
+                                float* dx, int accumulate, const float* mask, const float* add,
+                                int add_mode, int add_C, const float* bn_x, const float* bn_y,
+                                const float* bn_mean, const float* bn_istd, const float* bn_gamma,
+                                double* bn_part, void* stream) {
+  return run_conv_dgrad(k, b, Ci, H, W, Co, R, stride, pad, dy, params, pstride, dx, accumulate,
+                        mask, add, add_mode, add_C, bn_x, bn_y, bn_mean, bn_istd, bn_gamma,
+                        bn_part, stream, true);
 }
 
 size_t cb_test_bn_scratch_bytes(int k, int b, int C, int H, int W) {

@@ -147,3 +147,27 @@ def test_stale_library_is_refused(tmp_path):
     L, path = _stub(tmp_path, "current", "int cb_abi_version(void) { return %d; }\n" %
                     cb.ABI_VERSION)
     cb.check_abi(L, path)
+
+
+# (k, b, Ci, H, W, Co, R, stride, pad, forward by pointer, data gradient by pointer)
+BY_POINTER = [
+    (2, 32, 64, 56, 56, 256, 1, 1, 0, 0, 0),
+    (1, 41, 8, 112, 112, 1024, 3, 1, 1, 0, 0),   # dY of 2.11e9 bytes
+    (1, 42, 8, 112, 112, 1024, 3, 1, 1, 0, 1),   # 2.16e9
+    (9, 42, 1024, 112, 112, 8, 3, 1, 1, 1, 0),   # a replica's tensor counts, not the step's
+    (9, 41, 1024, 112, 112, 8, 3, 1, 1, 0, 0),
+    (1, 1, 32767, 128, 128, 1, 1, 1, 0, 0, 0),
+    (1, 1, 32768, 128, 128, 1, 1, 1, 0, 1, 0),   # exactly 2 GiB
+    (1, 1, 32768, 1, 1, 16384, 1, 1, 0, 1, 1),   # the filter
+    (1, 1, 32768, 1, 1, 16383, 1, 1, 0, 0, 0),
+    (1, 2731, 64, 224, 224, 64, 3, 2, 1, 1, 1),  # past 2^33 elements
+]
+
+
+@pytest.mark.parametrize("case", BY_POINTER)
+def test_conv_loads_by_tensor_size(case):
+    """Buffer loads mark zero elements by an offset of 2 GiB, which must lie past
+    the tensor they read."""
+    L = cb.lib()
+    assert [L.cb_test_conv_by_pointer(*case[:9], d) for d in (0, 1)] == list(case[9:])
+    assert L.cb_test_conv_by_pointer(*case[:6], 4, 1, 0, 0) == cb.CB_EINVAL

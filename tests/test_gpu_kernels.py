@@ -103,7 +103,7 @@ def _sample_idx(rng, shape, n):
 
 
 @pytest.mark.parametrize("case", CONV, ids=[c[0] for c in CONV])
-def test_conv_kernels(case):
+def test_conv_kernels(case, hook="cb_test_conv"):
     name, k, b, Ci, H, Co, R, st, pad, relu, bias, need_dx = case
     W = H
     Ho = (H + 2 * pad - R) // st + 1
@@ -130,10 +130,10 @@ def test_conv_kernels(case):
     scratch = torch.empty(scratch_n, dtype=torch.uint8, device="cuda")
     stats = torch.full((max(1, k * Co * parts * 2),), float("nan"), dtype=torch.float64,
                        device="cuda")
-    rc = L.cb_test_conv(k, b, Ci, H, W, Co, R, st, pad, relu, bias, xd.data_ptr(), pd.data_ptr(),
-                        pstride, yd.data_ptr(), stats.data_ptr() if parts else None, dyd.data_ptr(),
-                        dxd.data_ptr() if need_dx else None, gd.data_ptr(), scratch.data_ptr(),
-                        scratch_n, torch.cuda.current_stream().cuda_stream)
+    rc = getattr(L, hook)(k, b, Ci, H, W, Co, R, st, pad, relu, bias, xd.data_ptr(), pd.data_ptr(),
+                          pstride, yd.data_ptr(), stats.data_ptr() if parts else None, dyd.data_ptr(),
+                          dxd.data_ptr() if need_dx else None, gd.data_ptr(), scratch.data_ptr(),
+                          scratch_n, torch.cuda.current_stream().cuda_stream)
     assert rc == 0
     torch.cuda.synchronize()
     y, g = yd.cpu().numpy(), gd.cpu().numpy()
@@ -517,7 +517,7 @@ DGRAD_EPILOGUE = [
 
 
 @pytest.mark.parametrize("case", DGRAD_EPILOGUE, ids=[c[0] for c in DGRAD_EPILOGUE])
-def test_conv_data_gradient_epilogue(case):
+def test_conv_data_gradient_epilogue(case, hook="cb_test_conv_dgrad"):
     """One data-gradient launch with every epilogue operand, as cb_step uses
     it: accumulate, residual add (same shape or the option-A subsample),
     ReLU mask, and the fused batch-norm backward partial sums, against the
@@ -568,10 +568,10 @@ def test_conv_data_gradient_epilogue(case):
               istd=istd, g=gb if (bn and use_y in (2, 3)) else None).items()}
     part = torch.zeros(k * Ci * parts * 2, dtype=torch.float64, device="cuda") if bn else None
     ptr = lambda t: t.data_ptr() if t is not None else None
-    rc = L.cb_test_conv_dgrad(k, b, Ci, H, H, Co, R, st, pad, ptr(d["dy"]), ptr(d["p"]), pstride,
-                              ptr(d["dx"]), acc, ptr(d["mask"]), ptr(d["add"]), add_mode, add_C,
-                              ptr(d["x"]), ptr(d["y"]), ptr(d["mean"]), ptr(d["istd"]),
-                              ptr(d["g"]), ptr(part), torch.cuda.current_stream().cuda_stream)
+    rc = getattr(L, hook)(k, b, Ci, H, H, Co, R, st, pad, ptr(d["dy"]), ptr(d["p"]), pstride,
+                          ptr(d["dx"]), acc, ptr(d["mask"]), ptr(d["add"]), add_mode, add_C,
+                          ptr(d["x"]), ptr(d["y"]), ptr(d["mean"]), ptr(d["istd"]),
+                          ptr(d["g"]), ptr(part), torch.cuda.current_stream().cuda_stream)
     assert rc == 0
     torch.cuda.synchronize()
     got = d["dx"].cpu().numpy()
@@ -823,3 +823,76 @@ DGRAD_BUF = [
 @pytest.mark.parametrize("case", DGRAD_BUF, ids=[c[0] for c in DGRAD_BUF])
 def test_conv_data_gradient_buffer_loads(case):
     test_conv_kernels(case)
+
+
+def _kernels():
+    """The kernels of this thread's last hook call: forward, weight gradient, data gradient."""
+    return [cb.lib().cb_test_conv_kernel(i).decode() for i in range(3)]
+
+
+# The implicit GEMM's pointer loads, which tensors of 2 GiB and more take: every
+# filter size, stride and column tile, odd and even planes, padding or none
+POINTERS = [
+    ("ptr.1x1", 2, 3, 24, 9, 40, 1, 1, 0, 1, 1, 1),
+    ("ptr.1x1s2.grid", 2, 3, 70, 8, 45, 1, 2, 0, 0, 0, 1),
+    ("ptr.1x1s2.odd", 2, 3, 34, 7, 32, 1, 2, 0, 0, 0, 1),
+    ("ptr.1x1.n256", 2, 16, 16, 20, 256, 1, 1, 0, 0, 0, 1),
+    ("ptr.3x3", 2, 3, 7, 6, 19, 3, 1, 1, 0, 1, 1),
+    ("ptr.3x3.tap", 3, 5, 32, 13, 48, 3, 1, 1, 1, 1, 1),
+    ("ptr.3x3.rows", 32, 16, 12, 18, 14, 3, 1, 1, 0, 0, 1),
+    ("ptr.3x3s2", 3, 5, 7, 13, 19, 3, 2, 1, 0, 0, 1),
+    ("ptr.3x3s2.even", 2, 3, 20, 12, 33, 3, 2, 1, 0, 0, 1),
+    ("ptr.5x5", 2, 2, 17, 9, 21, 5, 1, 0, 0, 0, 1),
+    ("ptr.7x7s2", 2, 3, 3, 19, 5, 7, 2, 3, 0, 0, 0),
+]
+
+# columns as in DGRAD_EPILOGUE
+POINTERS_DGRAD = [
+    ("ptr.3x3.acc.mask.same.bn", 2, 3, 24, 12, 32, 3, 1, 1, 1, 1, 1, 24, 1, 1),
+    ("ptr.3x3s2.sub.bn", 2, 3, 20, 12, 33, 3, 2, 1, 0, 0, 2, 33, 1, 1),
+    ("ptr.1x1s2.grid.acc.mask.same.bn", 2, 3, 24, 14, 40, 1, 2, 0, 1, 1, 1, 24, 1, 1),
+]
+
+
+@pytest.mark.parametrize("case", POINTERS + POINTERS_DGRAD, ids=[c[0] for c in POINTERS + POINTERS_DGRAD])
+def test_conv_pointer_loads(case):
+    if len(case) == 12:
+        test_conv_kernels(case, "cb_test_conv_pointers")
+        assert _kernels()[0].endswith("by pointer")
+    else:
+        test_conv_data_gradient_epilogue(case, "cb_test_conv_dgrad_pointers")
+    assert case[-1] == 0 or "by pointer" in _kernels()[2]
+
+
+def test_conv_past_two_gib():
+    """X and dY of 2.2 GB: the zero border of a 3x3 layer holds where a buffer
+    offset past the tensor no longer reads 0.  Every image is the same, so
+    every image's y and dx must be those of one alone, to the last bit."""
+    L, b, C, H = cb.lib(), 685, 64, 112
+    s = torch.cuda.current_stream().cuda_stream
+    g = torch.Generator(device="cuda").manual_seed(0)
+    one = torch.randn(2, C, H, H, device="cuda", generator=g)
+    w = torch.randn(C * C * 9, device="cuda", generator=g) / 24.0
+    assert L.cb_test_conv_by_pointer(1, b, C, H, H, C, 3, 1, 1, 1) == 1
+
+    def run(x, dy, n, hook):
+        y, dx, gw = torch.empty_like(x), torch.empty_like(x), torch.empty_like(w)
+        sn = L.cb_test_conv_scratch_bytes(1, n, C, H, H, C, 3, 1, 1)
+        scratch = torch.empty(sn, dtype=torch.uint8, device="cuda")
+        assert getattr(L, hook)(1, n, C, H, H, C, 3, 1, 1, 0, 0, x.data_ptr(), w.data_ptr(), w.numel(),
+                                y.data_ptr(), None, dy.data_ptr(), dx.data_ptr(), gw.data_ptr(),
+                                scratch.data_ptr(), sn, s) == 0
+        torch.cuda.synchronize()
+        assert "by pointer" in _kernels()[0] and "by pointer" in _kernels()[2]
+        return y, dx, gw
+
+    y1, dx1, gw1 = run(one[:1], one[1:], 1, "cb_test_conv_pointers")
+    yo, dxo, _, _ = oracle.conv2d(one[:1].cpu().numpy()[:, :, :3], w.cpu().numpy().reshape(C, C, 3, 3),
+                                  None, 1, 1, dy=one[1:].cpu().numpy()[:, :, :3])
+    for got, ref in ((y1, yo), (dx1, dxo)):  # the first rows, the border among them
+        assert max_rel(got.cpu().numpy()[:, :, :2], ref[:, :, :2]) <= TOL_STEP1
+    x, dy = (t.expand(b, C, H, H).contiguous() for t in (one[:1], one[1:]))
+    y, dx, gw = run(x, dy, b, "cb_test_conv")
+    for got, ref in ((y, y1), (dx, dx1)):
+        assert all(bool((t == ref).all()) for t in got.split(64))
+    assert max_rel(gw.cpu().numpy(), gw1.cpu().numpy().astype(np.float64) * b) <= TOL_STEP1
