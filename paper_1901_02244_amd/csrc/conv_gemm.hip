@@ -533,7 +533,8 @@ __global__ __launch_bounds__(256, VEC && BM == 128 ? (BN == 64 ? 4 : 5) : 1) voi
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const int k = kq + i, co = k / RS, rs = k - co * RS;
-          // no && here: the compiler branches on it and then waits for loads in flight
+          // no && here: the compiler branched on it and then waited for the loads
+          // in flight (5x5, 882 -> 12 channels, 13x13, k=1 b=5: 903 us, now 701)
           rb[u][i] = buf_ld(wsrc, (row & (k < K)) ? (uint32_t)((co * N + n) * RS + rs) * 4u : OUTSIDE);
         }
       }
@@ -1378,7 +1379,7 @@ hipError_t launch_bwd_data(const ConvBwdDataArgs& a, hipStream_t s, const char**
   constexpr uint32_t shm = SP && BM == 128 && BN == 64 ? 8192 : 0;
   auto go = [&](auto ld) {
     constexpr int LD = decltype(ld)::value;
-    constexpr bool VEC = !SP && (LD != PLAIN || R == 5);
+    constexpr bool VEC = !SP && LD != PLAIN;
     constexpr int KIND = SP ? 3 : 1;
     if (VEC && vec_epilogue_ok(a)) {
       klaunch((conv_bwd_data_k<BM, BN, WM, WN, R, ST, BK, SP, LD, VEC>), grid, dim3(256), shm, s, a);
@@ -1392,13 +1393,7 @@ hipError_t launch_bwd_data(const ConvBwdDataArgs& a, hipStream_t s, const char**
   if (a.by_pointer || conv_by_pointer(a.g, true)) return go(std::integral_constant<int, PLAIN>());
   if constexpr (ST == 1 || SP)
     if (a.g.Co % BK == 0) return go(std::integral_constant<int, TAPS>());
-  // 5x5 layers with less than a workgroup per CU stay on the pointer loads,
-  // which skip what the window leaves out (882 -> 12 channels, 13x13, 14
-  // workgroups: the whole layer 951 us, by buffer 1032; with 2800 workgroups,
-  // 88 -> 3 channels, 106x106, 2595 and 2457).
-  const bool few = R == 5 && (int64_t)grid.x * grid.y * grid.z < MIN_WGS / 2;
-  if (!few) return go(std::integral_constant<int, BUF>());
-  return go(std::integral_constant<int, PLAIN>());
+  return go(std::integral_constant<int, BUF>());
 }
 
 constexpr int WG_BK = 32;  // pixels per stage of the weight gradient
