@@ -268,7 +268,10 @@ const char* cb_test_conv_kernel(int which);
 size_t cb_test_bn_scratch_bytes(int k, int b, int C, int H, int W);
 
 /* Batch norm with each replica's batch statistics over its b images, then
- * ReLU if relu; mean and istd (1/sqrt(var + 1e-5)) are written as [k][C]. */
+ * ReLU if relu; mean and istd (1/sqrt(var + 1e-5)) are written as [k][C].
+ * The norm takes its own sums: in one launch where the plane size and the
+ * pointers allow it, as cb_step runs its larger norms without a residual
+ * input, else in two. */
 int cb_test_bn_fwd(int k, int b, int C, int H, int W, int relu, const float* x,
                    const float* params, int64_t pstride, float* y, float* mean, float* istd,
                    void* scratch, size_t scratch_bytes, void* stream);
@@ -282,6 +285,17 @@ int cb_test_bn_bwd(int k, int b, int C, int H, int W, const float* x, const floa
                    int relu_x, const float* dy, const float* params, int64_t pstride,
                    const float* mean, const float* istd, float* dx, float* grads, void* scratch,
                    size_t scratch_bytes, void* stream);
+
+/* The same two with the sums and the apply always in launches of their own:
+ * the apply is the kernel of cb_step's norms whose sums come from the
+ * epilogue of a convolution. */
+int cb_test_bn_fwd_two(int k, int b, int C, int H, int W, int relu, const float* x,
+                       const float* params, int64_t pstride, float* y, float* mean, float* istd,
+                       void* scratch, size_t scratch_bytes, void* stream);
+int cb_test_bn_bwd_two(int k, int b, int C, int H, int W, const float* x, const float* mask_y,
+                       int relu_x, const float* dy, const float* params, int64_t pstride,
+                       const float* mean, const float* istd, float* dx, float* grads,
+                       void* scratch, size_t scratch_bytes, void* stream);
 
 /* Max pool K x K (first strict maximum wins, padded cells never win) on
  * [N][C][H][W]; with dy, its gradient dx (zeroed where x <= 0 if mask_relu).

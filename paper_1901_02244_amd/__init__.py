@@ -41,6 +41,7 @@ EXPORTS = (
     "cb_set_lr", "cb_restart", "cb_set_learners", "cb_learners", "cb_tuner_next",
     "cb_test_conv_dgrad_parts", "cb_test_conv_dgrad", "cb_set_graphs", "cb_test_conv_by_pointer",
     "cb_test_conv_pointers", "cb_test_conv_dgrad_pointers", "cb_test_conv_kernel",
+    "cb_test_bn_fwd_two", "cb_test_bn_bwd_two",
 )
 
 
@@ -133,6 +134,8 @@ def lib():
                                                 ctypes.c_size_t, _P]
         L.cb_test_bn_bwd.argtypes = [_i] * 5 + [_P, _P, _i, _P, _P, ctypes.c_int64, _P, _P, _P,
                                                 _P, _P, ctypes.c_size_t, _P]
+        L.cb_test_bn_fwd_two.argtypes = L.cb_test_bn_fwd.argtypes
+        L.cb_test_bn_bwd_two.argtypes = L.cb_test_bn_bwd.argtypes
         L.cb_test_maxpool.argtypes = [_i] * 7 + [_P, _P, _P, _P, _i, _P, _P]
         L.cb_test_softmax_xent.argtypes = [_i] * 3 + [_P, _P, _P, _P, _P]
         L.cb_test_conv_dgrad_parts.argtypes = [_i] * 9

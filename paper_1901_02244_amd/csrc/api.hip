@@ -49,7 +49,7 @@ struct Op {
   int res = -1, res_mode = RES_NONE, res_st = 1;
   int64_t mean = -1, istd = -1, dres = -1;
   int chunks = 1;
-  int parts = 0;                    // > 0: statistics come from the producing conv
+  int parts = 0;                    // > 0: statistics come from the producing conv, 0: its own
   int bwd_parts = 0;                // > 0: backward sums come from the next conv's dx
   // pooling
   int K = 0;
@@ -372,11 +372,13 @@ bool make_plan(const cb_model* m, int k, int b, Plan& p, int kcap = 0) {
     x.grad = take(bytes);
   }
   // a batch norm right after the conv that produces its input takes its
-  // statistics from that conv's epilogue
+  // statistics from that conv's epilogue, unless it is better off in one
+  // launch that takes its own
   for (size_t i = 1; i < p.ops.size(); ++i) {
     Op& o = p.ops[i];
     Op& prev = p.ops[i - 1];
-    if (o.kind == OP_BN && prev.kind == OP_CONV && prev.out == o.in) {
+    if (o.kind == OP_BN && prev.kind == OP_CONV && prev.out == o.in &&
+        !(o.res < 0 && bn_fwd_one_pays(k, b, o.C, o.H * o.W))) {
       prev.emit_stats = true;
       o.parts = conv_fwd_tiles_m(geom(p, prev));
     }
@@ -728,6 +730,10 @@ int enqueue_step(cb_ctx* c, const float* x, const int32_t* labels, hipStream_t s
         const double n = (double)N * o.C * o.H * o.W;
         const double res = a.res_mode == RES_SAME ? n
                            : a.res_mode == RES_SUBSAMPLE ? (double)N * a.res_C * o.H * o.W : 0.0;
+        if (o.parts == 0 && bn_fwd_one_ok(a)) {
+          CB_LAUNCH(c, "bn_one_k", 0.0, 4.0 * 2.0 * n, bn_fwd_one(a, s));
+          break;
+        }
         if (o.parts == 0) CB_LAUNCH(c, "bn_stats_k", 0.0, 4.0 * n, bn_fwd_stats(a, s));
         CB_LAUNCH(c, "bn_apply_k", 0.0, 4.0 * (2.0 * n + res), bn_fwd_apply(a, s, &nm_));
         break;

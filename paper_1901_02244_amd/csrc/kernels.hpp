@@ -294,6 +294,9 @@ hipError_t bn_bwd_apply(const BNBwdArgs& a, hipStream_t s, const char** name = n
 // Sums and apply in one launch, where the shapes and pointers allow it (part
 // is not used; forward without a residual input).
 bool bn_fwd_one_ok(const BNArgs& a);
+// Whether a norm without a residual input does better in that one launch than
+// with sums from the epilogue of the convolution before it.
+bool bn_fwd_one_pays(int k, int b, int C, int HW);
 hipError_t bn_fwd_one(const BNArgs& a, hipStream_t s);
 bool bn_bwd_one_ok(const BNBwdArgs& a);
 hipError_t bn_bwd_one(const BNBwdArgs& a, hipStream_t s);

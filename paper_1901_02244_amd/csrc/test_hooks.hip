@@ -218,9 +218,9 @@ size_t cb_test_bn_scratch_bytes(int k, int b, int C, int H, int W) {
   return (size_t)k * C * bn_chunks(b, H * W, C, k) * 2 * sizeof(double);
 }
 
-int cb_test_bn_fwd(int k, int b, int C, int H, int W, int relu, const float* x,
-                   const float* params, int64_t pstride, float* y, float* mean, float* istd,
-                   void* scratch, size_t scratch_bytes, void* stream) {
+static int run_bn_fwd(int k, int b, int C, int H, int W, int relu, const float* x,
+                      const float* params, int64_t pstride, float* y, float* mean, float* istd,
+                      void* scratch, size_t scratch_bytes, void* stream, bool two) {
   if (k < 1 || b < 1 || C < 1 || H < 1 || W < 1 || !x || !params || !y || !mean || !istd)
     return CB_EINVAL;
   if (scratch_bytes < cb_test_bn_scratch_bytes(k, b, C, H, W)) return CB_ENOMEM;
@@ -239,16 +239,30 @@ int cb_test_bn_fwd(int k, int b, int C, int H, int W, int relu, const float* x,
   a.res = nullptr;
   a.res_mode = RES_NONE;
   a.res_C = a.res_st = a.res_H = a.res_W = 0;
-  if (bn_fwd_one_ok(a)) return rc_of(bn_fwd_one(a, s));
+  if (!two && bn_fwd_one_ok(a)) return rc_of(bn_fwd_one(a, s));
   int rc = rc_of(bn_fwd_stats(a, s));
   if (rc) return rc;
   return rc_of(bn_fwd_apply(a, s));
 }
 
-int cb_test_bn_bwd(int k, int b, int C, int H, int W, const float* x, const float* mask_y,
-                   int relu_x, const float* dy, const float* params, int64_t pstride,
-                   const float* mean, const float* istd, float* dx, float* grads, void* scratch,
-                   size_t scratch_bytes, void* stream) {
+int cb_test_bn_fwd(int k, int b, int C, int H, int W, int relu, const float* x,
+                   const float* params, int64_t pstride, float* y, float* mean, float* istd,
+                   void* scratch, size_t scratch_bytes, void* stream) {
+  return run_bn_fwd(k, b, C, H, W, relu, x, params, pstride, y, mean, istd, scratch, scratch_bytes,
+                    stream, false);
+}
+
+int cb_test_bn_fwd_two(int k, int b, int C, int H, int W, int relu, const float* x,
+                       const float* params, int64_t pstride, float* y, float* mean, float* istd,
+                       void* scratch, size_t scratch_bytes, void* stream) {
+  return run_bn_fwd(k, b, C, H, W, relu, x, params, pstride, y, mean, istd, scratch, scratch_bytes,
+                    stream, true);
+}
+
+static int run_bn_bwd(int k, int b, int C, int H, int W, const float* x, const float* mask_y,
+                      int relu_x, const float* dy, const float* params, int64_t pstride,
+                      const float* mean, const float* istd, float* dx, float* grads, void* scratch,
+                      size_t scratch_bytes, void* stream, bool two) {
   if (k < 1 || b < 1 || C < 1 || H < 1 || W < 1 || !x || !dy || !params || !mean || !istd ||
       !dx || !grads || (mask_y && relu_x))
     return CB_EINVAL;
@@ -270,10 +284,26 @@ int cb_test_bn_bwd(int k, int b, int C, int H, int W, const float* x, const floa
   a.part = static_cast<double*>(scratch);
   a.chunks = bn_chunks(b, H * W, C, k);
   a.parts = a.chunks;
-  if (bn_bwd_one_ok(a)) return rc_of(bn_bwd_one(a, s));
+  if (!two && bn_bwd_one_ok(a)) return rc_of(bn_bwd_one(a, s));
   int rc = rc_of(bn_bwd_stats(a, s));
   if (rc) return rc;
   return rc_of(bn_bwd_apply(a, s));
+}
+
+int cb_test_bn_bwd(int k, int b, int C, int H, int W, const float* x, const float* mask_y,
+                   int relu_x, const float* dy, const float* params, int64_t pstride,
+                   const float* mean, const float* istd, float* dx, float* grads, void* scratch,
+                   size_t scratch_bytes, void* stream) {
+  return run_bn_bwd(k, b, C, H, W, x, mask_y, relu_x, dy, params, pstride, mean, istd, dx, grads,
+                    scratch, scratch_bytes, stream, false);
+}
+
+int cb_test_bn_bwd_two(int k, int b, int C, int H, int W, const float* x, const float* mask_y,
+                       int relu_x, const float* dy, const float* params, int64_t pstride,
+                       const float* mean, const float* istd, float* dx, float* grads,
+                       void* scratch, size_t scratch_bytes, void* stream) {
+  return run_bn_bwd(k, b, C, H, W, x, mask_y, relu_x, dy, params, pstride, mean, istd, dx, grads,
+                    scratch, scratch_bytes, stream, true);
 }
 
 int cb_test_maxpool(int N, int C, int H, int W, int K, int stride, int pad, const float* x,

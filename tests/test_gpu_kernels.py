@@ -200,7 +200,7 @@ BN = [
 
 
 @pytest.mark.parametrize("case", BN, ids=[c[0] for c in BN])
-def test_batchnorm_kernels(case):
+def test_batchnorm_kernels(case, form=""):
     name, k, b, C, H, relu = case
     W = H
     rng = _rng("bn" + name)
@@ -231,13 +231,13 @@ def test_batchnorm_kernels(case):
     istd = torch.empty(k * C, dtype=torch.float32, device="cuda")
     scratch = torch.empty(sn, dtype=torch.uint8, device="cuda")
     st = torch.cuda.current_stream().cuda_stream
-    assert L.cb_test_bn_fwd(k, b, C, H, W, relu, xd.data_ptr(), pd.data_ptr(), pstride,
+    assert getattr(L, "cb_test_bn_fwd" + form)(k, b, C, H, W, relu, xd.data_ptr(), pd.data_ptr(), pstride,
                             yd.data_ptr(), mean.data_ptr(), istd.data_ptr(), scratch.data_ptr(),
                             sn, st) == 0
     mask = _dev(yo.astype(np.float32)) if relu else None
     dxd = torch.empty_like(xd)
     gd = torch.zeros_like(pd)
-    assert L.cb_test_bn_bwd(k, b, C, H, W, xd.data_ptr(), mask.data_ptr() if relu else None, 0,
+    assert getattr(L, "cb_test_bn_bwd" + form)(k, b, C, H, W, xd.data_ptr(), mask.data_ptr() if relu else None, 0,
                             dyd.data_ptr(), pd.data_ptr(), pstride, mean.data_ptr(),
                             istd.data_ptr(), dxd.data_ptr(), gd.data_ptr(), scratch.data_ptr(), sn,
                             st) == 0
@@ -267,7 +267,7 @@ def _bn_relu_from_x(x, mean, istd, gam, bet):
 
 
 @pytest.mark.parametrize("case", [c for c in BN if c[-1]], ids=[c[0] for c in BN if c[-1]])
-def test_batchnorm_backward_relu_mask_from_x(case):
+def test_batchnorm_backward_relu_mask_from_x(case, form=""):
     """A norm with a ReLU and no residual input: the backward recomputes the
     ReLU decision from x and takes exactly the forward's (checked bitwise
     against the forward's output), and its gradients match the oracle's
@@ -290,12 +290,12 @@ def test_batchnorm_backward_relu_mask_from_x(case):
     istd = torch.empty(k * C, dtype=torch.float32, device="cuda")
     scratch = torch.empty(sn, dtype=torch.uint8, device="cuda")
     st = torch.cuda.current_stream().cuda_stream
-    assert L.cb_test_bn_fwd(k, b, C, H, W, 1, xd.data_ptr(), pd.data_ptr(), pstride,
+    assert getattr(L, "cb_test_bn_fwd" + form)(k, b, C, H, W, 1, xd.data_ptr(), pd.data_ptr(), pstride,
                             yd.data_ptr(), mean.data_ptr(), istd.data_ptr(), scratch.data_ptr(),
                             sn, st) == 0
     dxd = torch.empty_like(xd)
     gd = torch.zeros_like(pd)
-    assert L.cb_test_bn_bwd(k, b, C, H, W, xd.data_ptr(), None, 1, dyd.data_ptr(), pd.data_ptr(),
+    assert getattr(L, "cb_test_bn_bwd" + form)(k, b, C, H, W, xd.data_ptr(), None, 1, dyd.data_ptr(), pd.data_ptr(),
                             pstride, mean.data_ptr(), istd.data_ptr(), dxd.data_ptr(),
                             gd.data_ptr(), scratch.data_ptr(), sn, st) == 0
     torch.cuda.synchronize()
@@ -335,6 +335,14 @@ def test_batchnorm_one_launch(case):
     test_batchnorm_kernels(case)
     if case[-1]:
         test_batchnorm_backward_relu_mask_from_x(case)
+
+
+@pytest.mark.parametrize("case", BN + BN_ONE, ids=[c[0] for c in BN + BN_ONE])
+def test_batchnorm_two_launches(case):
+    """The sums and the apply in launches of their own, at the same shapes."""
+    test_batchnorm_kernels(case, "_two")
+    if case[-1]:
+        test_batchnorm_backward_relu_mask_from_x(case, "_two")
 
 
 # (name, N, C, H, W, K, stride, pad, mask_relu)

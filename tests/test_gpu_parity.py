@@ -555,6 +555,23 @@ def test_resnet32_ragged_batch():
     p.summary(f"z rel-L2 {p.z_error():.2e}")
 
 
+def test_resnet32_norms_in_one_launch():
+    """16 learners give the 16-channel norms without a residual input the 256
+    channels from which they take their own sums in one launch; the others
+    take theirs from the convolutions."""
+    p = Pair("resnet32", 3, 16, 16, 10, k=16, b=2, seed=4)
+    p.gpu.cb_profile_enable()
+    p.step(0)
+    torch.cuda.synchronize()
+    names = p.gpu.cb_profile()
+    assert names["bn_one_k"][0] == 16, names  # the stem's norm and each block's first
+    assert sum(n[0] for name, n in names.items() if name.startswith("bn_apply")) == 15, names
+    p.gpu.cb_profile_enable(False)
+    p.check_grads()
+    p.sync(verbose=True)
+    p.summary()
+
+
 def test_resnet32_odd_feature_maps():
     """28 x 28 images: stage 3 runs on 7 x 7 maps (the implicit-GEMM paths
     with odd sizes, a global average over 49 pixels)."""
