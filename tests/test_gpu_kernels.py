@@ -98,6 +98,11 @@ def _rng(tag):
     return np.random.default_rng(zlib.crc32(tag.encode()))
 
 
+def _kernels():
+    """The kernels of this thread's last hook call: forward, weight gradient, data gradient."""
+    return [cb.lib().cb_test_conv_kernel(i).decode() for i in range(3)]
+
+
 def _sample_idx(rng, shape, n):
     return np.stack([rng.integers(0, d, n) for d in shape], axis=1).astype(np.int32)
 
@@ -524,6 +529,9 @@ DGRAD_EPILOGUE = [
 ]
 
 
+DGRAD_LOADS = {"gemm.3x3s2": "", "gemm.5x5": "", "gemm.tap": "tap-major"}
+
+
 @pytest.mark.parametrize("case", DGRAD_EPILOGUE, ids=[c[0] for c in DGRAD_EPILOGUE])
 def test_conv_data_gradient_epilogue(case, hook="cb_test_conv_dgrad"):
     """One data-gradient launch with every epilogue operand, as cb_step uses
@@ -582,6 +590,9 @@ def test_conv_data_gradient_epilogue(case, hook="cb_test_conv_dgrad"):
                           ptr(d["g"]), ptr(part), torch.cuda.current_stream().cuda_stream)
     assert rc == 0
     torch.cuda.synchronize()
+    for prefix, loads in DGRAD_LOADS.items():
+        if name.startswith(prefix):
+            _assert_loads(_kernels()[2], loads)
     got = d["dx"].cpu().numpy()
     sums = part.cpu().numpy().reshape(k, Ci, parts, 2).sum(axis=2) if bn else None
     for j in range(k):
@@ -611,6 +622,7 @@ def test_conv_data_gradient_epilogue(case, hook="cb_test_conv_dgrad"):
 # The GEMM data gradient's float4 epilogue (planes of a multiple of four
 # pixels): every tile width, quads that straddle rows, the subsampled shortcut;
 # columns as in DGRAD_EPILOGUE
+# (a subsampled shortcut at stride 1, which no network has, takes the scalar one)
 DGRAD_VEC = [
     ("vec.3x3s2.acc.mask.sub.bn", 2, 3, 20, 12, 33, 3, 2, 1, 1, 1, 2, 33, 1, 1),
     ("vec.3x3s2.w6.sub.bn", 1, 2, 7, 6, 19, 3, 2, 1, 0, 0, 2, 19, 1, 0),
@@ -626,6 +638,7 @@ DGRAD_VEC = [
 @pytest.mark.parametrize("case", DGRAD_VEC, ids=[c[0] for c in DGRAD_VEC])
 def test_conv_data_gradient_vector_epilogue(case):
     test_conv_data_gradient_epilogue(case)
+    assert _kernels()[2].endswith(" float4") == (case[0] != "vec.3x3.sub.bn"), _kernels()
 
 
 @pytest.mark.parametrize("R,st,H,Ci,add_mode", [(3, 2, 12, 24, 2), (3, 2, 40, 72, 1), (1, 1, 6, 40, 1)])
@@ -650,13 +663,14 @@ def test_gemm_data_gradient_at_any_float_alignment(R, st, H, Ci, add_mode):
                                     bnx.data_ptr(), bny.data_ptr(), m[0].data_ptr(),
                                     m[1].data_ptr(), None, pt.data_ptr(), s) == 0
         torch.cuda.synchronize()
+        assert _kernels()[2].endswith(" float4") == (off == 0)
         outs.append([t.cpu().numpy() for t in (dx, pt)])
     for a, c in zip(*outs):
         assert np.isfinite(a).all() and np.array_equal(a, c)
 
 
 # 3x3 stride-1 layers on the direct kernel's flat pixel tiles: per width the
-# fewest channels at these batches that reach each tile (one case below the
+# fewest channels at these batches that reach each tile (the case below the
 # 14-wide rule stays on the GEMM), with last tiles that are partial and tiles
 # that span two or more images
 FLAT = [
@@ -684,6 +698,8 @@ FLAT_DGRAD = [
 @pytest.mark.parametrize("case", FLAT + FLAT_DGRAD, ids=[c[0] for c in FLAT + FLAT_DGRAD])
 def test_conv_flat_tiles(case):
     (test_conv_kernels if len(case) == 12 else test_conv_data_gradient_epilogue)(case)
+    kernel = _kernels()[0 if len(case) == 12 else 2]
+    assert kernel.startswith("conv_fwd_k" if case[0].endswith("below") else "conv3x3_flat_k"), kernel
 
 
 # (W, channels, k, b, dX at an inner pixel): flat data gradients and, with fewer
@@ -712,6 +728,8 @@ def test_conv_data_gradient_tap_order(W, C, k, b, want):
                                        torch.cuda.current_stream().cuda_stream) == 0
     torch.cuda.synchronize()
     assert (dx[:, :, 1:-1, 1:-1] == want).all()
+    flat = W == 8 or (C >= 448 and W != 56 and k * b > 1)
+    assert _kernels()[2].startswith("conv3x3_flat_k") == flat, _kernels()
 
 
 @pytest.mark.parametrize("W,C", [(14, 512), (16, 32), (32, 16)])
@@ -768,6 +786,10 @@ WGRAD_QUADS = [
 @pytest.mark.parametrize("case", WGRAD_QUADS, ids=[c[0] for c in WGRAD_QUADS])
 def test_conv_weight_gradient_quads(case):
     test_conv_kernels(case)
+    name, Co, kernel = case[0], case[5], _kernels()[1]
+    # dY and X in quads; dY alone from 64 rows a tile (more than 32 channels); pixels
+    form = "true, true" if name.startswith("quads.flat") else "true, false" if Co > 32 else "false, false"
+    assert kernel.startswith("conv_bwd_weight_k<") and kernel.endswith(form + ">"), kernel
 
 
 @pytest.mark.parametrize("R,H,xo,dyo", [(1, 6, 1, 0), (1, 6, 0, 1), (3, 6, 1, 1)])
@@ -795,13 +817,16 @@ def test_conv_weight_gradient_at_any_float_alignment(R, H, xo, dyo):
 
 
 # the flat weight gradient: splits whose last stage is partial, a last split
-# and a last quad group that are partial, stages that span images, one split
+# and a last quad group that are partial, stages that span images, one split;
+# splits below the rule's pixels stay on the GEMM
 WGRAD_FLAT = [
     ("wgflat.w14", 1, 27, 96, 14, 160, 3, 1, 1, 0, 0, 0),
     ("wgflat.w14.one.split", 32, 1, 128, 14, 128, 3, 1, 1, 0, 1, 0),
-    ("wgflat.w14.ragged", 3, 9, 32, 14, 416, 3, 1, 1, 0, 0, 0),
+    ("wgflat.w14.ragged", 3, 13, 32, 14, 416, 3, 1, 1, 0, 0, 0),
+    ("wgflat.w14.below", 3, 9, 32, 14, 416, 3, 1, 1, 0, 0, 0),
     ("wgflat.w28", 32, 4, 32, 28, 32, 3, 1, 1, 0, 0, 0),
-    ("wgflat.w28.ragged", 8, 3, 96, 28, 64, 3, 1, 1, 0, 0, 0),
+    ("wgflat.w28.ragged", 8, 5, 96, 28, 64, 3, 1, 1, 0, 0, 0),
+    ("wgflat.w28.below", 8, 3, 96, 28, 64, 3, 1, 1, 0, 0, 0),
     ("wgflat.w56", 32, 1, 32, 56, 32, 3, 1, 1, 0, 1, 0),
     ("wgflat.w56.b2", 6, 2, 64, 56, 96, 3, 1, 1, 0, 0, 0),
 ]
@@ -810,6 +835,9 @@ WGRAD_FLAT = [
 @pytest.mark.parametrize("case", WGRAD_FLAT, ids=[c[0] for c in WGRAD_FLAT])
 def test_conv_weight_gradient_flat(case):
     test_conv_kernels(case)
+    kernel = _kernels()[1]
+    assert kernel.startswith("conv_bwd_weight_k" if case[0].endswith("below")
+                             else "conv3x3_flat_wgrad_k"), kernel
 
 
 # GEMM data gradients by masked buffer loads in the order (co, r, s): strides,
@@ -823,6 +851,8 @@ DGRAD_BUF = [
     ("buf.1x1s2.grid", 2, 3, 70, 8, 45, 1, 2, 0, 0, 0, 1),
     ("buf.1x1s2.odd", 2, 3, 34, 7, 32, 1, 2, 0, 0, 0, 1),
     ("buf.5x5.pad0", 2, 2, 17, 9, 21, 5, 1, 0, 0, 0, 1),
+    ("buf.5x5.wide", 3, 9, 40, 20, 9, 5, 1, 2, 0, 0, 1),
+    ("buf.5x5.rows256", 8, 21, 3, 30, 5, 5, 1, 2, 0, 0, 1),
     ("buf.3x3.wide", 4, 9, 130, 11, 23, 3, 1, 1, 0, 0, 1),
     ("buf.1x1pad", 1, 2, 20, 5, 37, 1, 1, 1, 0, 0, 1),
 ]
@@ -831,11 +861,16 @@ DGRAD_BUF = [
 @pytest.mark.parametrize("case", DGRAD_BUF, ids=[c[0] for c in DGRAD_BUF])
 def test_conv_data_gradient_buffer_loads(case):
     test_conv_kernels(case)
+    _assert_loads(_kernels()[2], "")
 
 
-def _kernels():
-    """The kernels of this thread's last hook call: forward, weight gradient, data gradient."""
-    return [cb.lib().cb_test_conv_kernel(i).decode() for i in range(3)]
+def _assert_loads(kernel, loads, float4=None):
+    """An implicit-GEMM data gradient with these loads ("", buffers in the order
+    (co, r, s); "tap-major"; "by pointer") and, if given, epilogue."""
+    assert kernel.startswith("conv_bwd_data_k<"), kernel
+    if float4 is not None:
+        assert kernel.endswith(" float4") == float4, kernel
+    assert kernel.removesuffix(" float4").split(">")[1].strip() == loads, kernel
 
 
 # The implicit GEMM's pointer loads, which tensors of 2 GiB and more take: every
