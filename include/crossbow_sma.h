@@ -213,7 +213,8 @@ int cb_tuner_next(int l, double t, double t_prev, double threshold, int l_max);
 
 /* --- operator test hooks ------------------------------------------------
  * One operator of the learning task on caller device buffers, through the
- * same launchers (kernels and tile choices) that cb_step uses, enqueued on
+ * same launchers (kernels and tile choices) that cb_step uses, except where
+ * a hook says that it forces another form, enqueued on
  * `stream` (a hipStream_t).  k replicas of b images; the parameters of
  * replica j start at params + j*pstride (weight, then bias if any; for batch
  * norm gamma then beta), and gradients land in the same layout in grads.

@@ -118,9 +118,8 @@ __device__ __forceinline__ double shfl_xor_d(double v, int o) { return __shfl_xo
 enum ConvLoad { PLAIN, TAPS, BUF };
 
 // LD BUF, PLAIN: the contraction runs over k = (ci, r, s).  LD TAPS (Ci a
-// multiple of BK): over k = (channel block of
-// BK, r, s, channel in the block), the same sum in
-// another order (the same order for 1x1 filters).  A stage of BK steps then
+// multiple of BK): over k = (channel block of BK, r, s, channel in the block),
+// the same sum in another order (the same order for 1x1 filters).  A stage of BK steps then
 // shares one tap (r, s), so its window check and tap offset are computed
 // once per stage, and a thread's steps are consecutive channels (one plane
 // apart in X, RS floats apart in W); the R*R taps of a channel block follow
@@ -1332,8 +1331,9 @@ const char* load_name() {
 // LDS stage depth: 32 contraction steps, 16 for tiles of 128 rows or more
 // (the 1x1 stride-2 grid-only data gradient from 256 rows: its 128-row
 // tiles measured slower with 16).  The shallow stage halves the LDS of a
-// 128 x 64 tile (32 KB), so five workgroups share a CU instead of two, and
-// one workgroup's epilogue traffic overlaps the others' MFMAs (ResNet-50
+// 128 x 64 tile (26 KB), so four workgroups, which their registers allow,
+// share a CU, and one workgroup's epilogue traffic overlaps the others' MFMAs
+// (measured with rows padded in LDS, two workgroups against five; ResNet-50
 // k=2 b=32: 1x1 data gradients 147 -> 130 us, 1x1 forward 104 -> 96 us, 3x3
 // data gradients 252 -> 228 us; with the tap-major loaders the 3x3 forward
 // 211 -> 206 us).
@@ -1398,7 +1398,7 @@ hipError_t launch_bwd_data(const ConvBwdDataArgs& a, hipStream_t s, const char**
 
 constexpr int WG_BK = 32;  // pixels per stage of the weight gradient
 
-// 128-row tiles stage 16 pixels (30 KB of LDS, five workgroups per CU);
+// 128-row tiles stage 16 pixels (24 KB of LDS, five workgroups per CU);
 // the others 32.  Split chunks are whole multiples of WG_BK either way.
 template <int BM, int BN, int WM, int WN, int R>
 hipError_t launch_bwd_weight(const ConvBwdWeightArgs& a, hipStream_t s, const char** name) {

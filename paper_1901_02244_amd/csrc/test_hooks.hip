@@ -1,7 +1,8 @@
 // test_hooks.hip -- one operator of the learning task on caller buffers.
 //
 // These entry points run the same launchers (and so the same kernels and
-// tile choices) as cb_step, on device buffers the caller fills, so each
+// tile choices) as cb_step, or (*_pointers, *_two) another form that large
+// tensors or other layers take, on device buffers the caller fills, so each
 // kernel can be compared with a reference at any shape, including the
 // exact layer shapes of the training workloads.  Nothing here allocates:
 // scratch comes from the caller, sized by the *_scratch_bytes calls.
