@@ -59,26 +59,29 @@ __device__ __forceinline__ GemmTile gemm_tile() {
 // contraction steps by row, 16 bytes each, the row xored with a swizzle of
 // the quad.  The 16 lanes that a 16-byte read serves together take lanes 0-3
 // and 12-15 of one quad's 16 rows and 4-11 of the next one's, and those of a
-// write that stores four quads per row four rows of each: both fall on
-// distinct banks.  (Rows padded to BK + 4 floats had 0.5 to 0.65 conflict
-// cycles per useful one, and a fifth more LDS.)  ONE: quads 4 to 7 also xor the
-// row with 2, for a stage that is stored one float per lane, two rows of
-// eight quads at a time: otherwise quads q and q + 4 of a row share banks.
-template <int ROWS, bool ONE = false>
+// write that stores four quads per row four rows of each: both are laid out to
+// fall on distinct banks.  Conflict cycles counted per useful one (ResNet-50):
+// 0.14 to 0.16 in the forward and the data gradients, 0.5 in the weight
+// gradients; with rows padded to BK + 4 floats, which also take a fifth more
+// LDS, 0.5 to 0.65 and 0.5 to 1.0.  UP: quads 4 to 7 also xor the row with 2, for
+// the 32-pixel stages of the weight gradient, stored two rows of eight quads
+// at a time: otherwise quads q and q + 4 of a row share banks (1.5; 1x1, 256 ->
+// 64 channels 56x56, k=2 b=32: 77.4 us, with UP 73.6).
+template <int ROWS, bool UP = false>
 __device__ __forceinline__ int quad_at(int row, int quad) {
-  return quad * ROWS + (row ^ (0x84c0 >> (4 * (quad & 3)) & 12) ^ (ONE ? (quad & 4) >> 1 : 0));
+  return quad * ROWS + (row ^ (0x84c0 >> (4 * (quad & 3)) & 12) ^ (UP ? (quad & 4) >> 1 : 0));
 }
 
 // One LDS stage: the products of A rows wm0 + 16 i and B rows wn0 + 16 i.
-template <int BM, int BN, int TM, int TN, int BK, bool ONE = false>
+template <int BM, int BN, int TM, int TN, int BK, bool UP = false>
 __device__ __forceinline__ void mma_stage(const v4f* As, const v4f* Bs, int wm0, int wn0,
                                           int lane, v4f (&acc)[TM][TN]) {
   const int ra = wm0 + (lane & 15), rb = wn0 + (lane & 15), q = lane >> 4;
   const int a0 = quad_at<BM>(ra, q), b0 = quad_at<BN>(rb, q);
 #pragma unroll
   for (int g = 0; g < BK; g += 16) {
-    const v4f* Ar = As + (ONE && g ? quad_at<BM, true>(ra, q + 4) : a0 + g / 4 * BM);
-    const v4f* Br = Bs + (ONE && g ? quad_at<BN, true>(rb, q + 4) : b0 + g / 4 * BN);
+    const v4f* Ar = As + (UP && g ? quad_at<BM, true>(ra, q + 4) : a0 + g / 4 * BM);
+    const v4f* Br = Bs + (UP && g ? quad_at<BN, true>(rb, q + 4) : b0 + g / 4 * BN);
     v4f av[TM], bv[TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i) av[i] = Ar[i * 16];
@@ -893,7 +896,7 @@ __global__ __launch_bounds__(256, VEC && BM == 128 ? (BN == 64 ? 4 : 5) : 1) voi
 // by its loads: ResNet-50's flat layers (k=2 b=32) took 92 us per launch with
 // one pixel per load and take 73 with quads; its 7 x 7 layers measured slower
 // with four single loads per row (1x1 93 -> 135, 3x3 236 -> 289 us).  One pixel
-// at a time, with a quad's row xor (quad_at's ONE) and the LDS places from a
+// at a time, with a quad's row xor (quad_at's UP) and the LDS places from a
 // few bases, and 16-row tiles held to seven waves per SIMD by the launch
 // bounds: 48 -> 16 channels 5x5, 62x62, k=5 b=32 555 -> 530 us, 16 -> 16 3x3, 40x40,
 // k=4 b=32 37.2 -> 36.0.
@@ -1000,13 +1003,13 @@ __global__ __launch_bounds__(256, BM == 16 && !QUADS ? 7 : 1) void conv_bwd_weig
   };
   // LDS places of this thread's rows rg, rg + RG, ...: the swizzle repeats
   // every 16 rows, so NB bases and constant steps of 16 rows reach them all
-  constexpr bool ONE = !QUADS && BK == 32;
+  constexpr bool UP = BK == 32;
   constexpr int NB = RG < 16 ? 16 / RG : 1;
   int pa[NB], pb[NB];
 #pragma unroll
   for (int i = 0; i < NB; ++i) {
-    pa[i] = quad_at<BM, ONE>(rg + RG * i, PX * q4 / 4);
-    pb[i] = quad_at<BN, ONE>(rg + RG * i, PX * q4 / 4);
+    pa[i] = quad_at<BM, UP>(rg + RG * i, PX * q4 / 4);
+    pb[i] = quad_at<BN, UP>(rg + RG * i, PX * q4 / 4);
   }
   auto put = [&](v4f* quad, vpx v) {
     reinterpret_cast<vpx*>(quad)[QUADS ? 0 : q4 & 3] = v;
@@ -1035,7 +1038,7 @@ __global__ __launch_bounds__(256, BM == 16 && !QUADS ? 7 : 1) void conv_bwd_weig
       advance();
       load();
     }
-    mma_stage<BM, BN, TM, TN, BK, ONE>(As[cur], Bs[cur], wm0, wn0, lane, acc);
+    mma_stage<BM, BN, TM, TN, BK, UP>(As[cur], Bs[cur], wm0, wn0, lane, acc);
     if (t + 1 < T) store(cur ^ 1);
     __syncthreads();
   }
